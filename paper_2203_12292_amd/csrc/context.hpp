@@ -42,7 +42,7 @@ struct Level {
   // transfer from level l-1 (fine side = this level)
   bool has_transfer = false;
   DeviceArray<int32_t> tr_ident_c, tr_ident_f, tr_ref_c, tr_ref_f;
-  DeviceArray<uint8_t> tr_valence;
+  DeviceArray<int32_t> tr_ident_fdesc, tr_ident_cdesc, tr_ref_fdesc, tr_ref_cdesc;
   TransferView tview;
   // local smoothing: refinement-edge DoFs, and the copy to / from the active
   // mesh (level DoF cp_level[q] <-> active DoF cp_active[q])

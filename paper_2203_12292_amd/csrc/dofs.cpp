@@ -559,35 +559,6 @@ TransferDofs build_transfer(const LevelDofs& fine, const LevelDofs& coarse, bool
   MFMG_REQUIRE(static_cast<int64_t>(group_cells.size()) == nf, MFMG_ERR_INVALID_ARG,
                "transfer groups do not cover the fine mesh");
 
-  // valence: number of groups in which an entity appears unconstrained
-  std::vector<uint8_t> count(fine.n_entities, 0);
-  std::vector<int32_t> seen;
-  for (int64_t g = 0; g < ncc; ++g) {
-    seen.clear();
-    for (int64_t q = group_start[g]; q < group_start[g + 1]; ++q) {
-      const int32_t c = group_cells[q];
-      for (int s = 0; s < N_SLOTS; ++s) {
-        const int32_t id = fine.ent_id[s * nf + c];
-        if (id < 0 || fine.slot_hanging(c, s)) continue;
-        seen.push_back(id);
-      }
-    }
-    std::sort(seen.begin(), seen.end());
-    seen.erase(std::unique(seen.begin(), seen.end()), seen.end());
-    for (int32_t id : seen) {
-      MFMG_REQUIRE(count[id] < TRANSFER_OWNER - 1, MFMG_ERR_INVALID_ARG, "valence overflow");
-      ++count[id];
-    }
-  }
-  T.valence.assign(N_SLOTS * nf, 0);
-  for (int64_t c = 0; c < nf; ++c)
-    for (int s = 0; s < N_SLOTS; ++s) {
-      const int32_t id = fine.ent_id[s * nf + c];
-      if (id < 0 || fine.slot_hanging(c, s)) continue;
-      MFMG_REQUIRE(count[id] > 0 && count[id] < TRANSFER_OWNER, MFMG_ERR_INVALID_ARG,
-                   "entity without a transfer group, or valence overflow");
-      T.valence[s * nf + c] = count[id];
-    }
   if (coloured) {  // group lists in colour order (the restriction's coarse entities)
     std::vector<int64_t> order;
     const std::vector<int32_t> ic = T.ident_coarse, jf = T.ident_fine;
@@ -606,38 +577,58 @@ TransferDofs build_transfer(const LevelDofs& fine, const LevelDofs& coarse, bool
       for (int ch = 0; ch < 8; ++ch) T.refined_fine[ch * nrg + q] = rf[ch * nrg + order[q]];
     }
   }
-  // owner: of the (fine cell, slot) pairs through which the transfer kernels
-  // reach an unconstrained entity, the first one (identity groups, then
-  // refinement groups, nodes in lattice order); every other pair skips it.
-  // A refinement group's lattice has 2k+1 nodes per axis, node I belonging
-  // to child I >= k (local node I - k), so an entity on a face between
-  // children is reached through one child only.
-  const int kf = fine.k;
-  std::vector<uint8_t> claimed(fine.n_entities, 0);
-  auto visit = [&](int64_t f, int a, int b, int c) {
-    const int s = node_slot(a, b, c, kf);
-    uint8_t& v = T.valence[s * nf + f];
-    if (v == 0) return;  // constrained or Dirichlet
-    const int32_t id = fine.ent_id[s * nf + f];
-    if (!claimed[id]) {
-      claimed[id] = 1;
-      v |= TRANSFER_OWNER;
+  // Records of the groups.  Owner: of the (group, lattice entity) pairs
+  // through which the transfer kernels reach an unconstrained fine entity, the
+  // first one (identity groups, then refinement groups, nodes in lattice
+  // order); every other pair gets -1.  A refinement group's lattice has 2k+1
+  // nodes per axis; an entity on a face between children is seen through the
+  // child with the higher index.
+  std::vector<uint8_t> claimed(fine.n_entities, 0), wanted(fine.n_entities, 0);
+  for (int64_t f = 0; f < nf; ++f)
+    for (int s = 0; s < N_SLOTS; ++s) {
+      const int32_t id = fine.ent_id[s * nf + f];
+      if (id >= 0 && !fine.slot_hanging(f, s)) wanted[id] = 1;
     }
+  auto record = [&](int64_t f, int s) -> int32_t {
+    const int32_t id = fine.ent_id[s * nf + f];
+    if (id < 0 || fine.slot_hanging(f, s) || claimed[id]) return -1;
+    claimed[id] = 1;
+    return fine.ent_size[id] > 0 ? fine.ent[s * nf + f] : -1;
   };
-  for (size_t q = 0; q < T.ident_fine.size(); ++q)
-    for (int c = 0; c <= kf; ++c)
-      for (int b = 0; b <= kf; ++b)
-        for (int a = 0; a <= kf; ++a) visit(T.ident_fine[q], a, b, c);
-  const int64_t nr = static_cast<int64_t>(T.refined_coarse.size());
-  for (int64_t r = 0; r < nr; ++r)
-    for (int L = 0; L <= 2 * kf; ++L)
-      for (int J = 0; J <= 2 * kf; ++J)
-        for (int I = 0; I <= 2 * kf; ++I) {
-          const int cx = I >= kf, cy = J >= kf, cz = L >= kf;
-          visit(T.refined_fine[(cx + 2 * cy + 4 * cz) * nr + r], I - cx * kf, J - cy * kf, L - cz * kf);
-        }
-  for (int64_t e = 0; e < fine.n_entities; ++e)  // (entities without DoFs, e.g. edges at k = 1, need none)
-    MFMG_REQUIRE(count[e] == 0 || fine.ent_size[e] == 0 || claimed[e], MFMG_ERR_INVALID_ARG,
+  auto slot3 = [](int ca, int cb, int cc) { return node_slot(ca, cb, cc, 2); };  // classes 0, 1, 2 are degree-2 nodes
+  auto coarse_record = [&](std::vector<int32_t>& out, size_t g, int64_t c) {
+    int32_t* r = &out[g * transfer_record(3)];
+    for (int e = 0; e < 27; ++e) {
+      const int s = slot3(e % 3, (e / 3) % 3, e / 9);
+      r[e] = slot_size(s, coarse.k) > 0 ? coarse.ent[s * ncc + c] : -1;
+    }
+    r[27] = static_cast<int32_t>(coarse.mask[c]);
+  };
+  const size_t ni = T.ident_fine.size(), nrg = T.refined_coarse.size();
+  T.ident_fdesc.assign(ni * transfer_record(3), -1);
+  T.ident_cdesc.assign(ni * transfer_record(3), -1);
+  T.refined_fdesc.assign(nrg * transfer_record(5), -1);
+  T.refined_cdesc.assign(nrg * transfer_record(3), -1);
+  for (size_t g = 0; g < ni; ++g) {
+    for (int e = 0; e < 27; ++e)
+      T.ident_fdesc[g * transfer_record(3) + e] = record(T.ident_fine[g], slot3(e % 3, (e / 3) % 3, e / 9));
+    coarse_record(T.ident_cdesc, g, T.ident_coarse[g]);
+  }
+  for (size_t g = 0; g < nrg; ++g) {
+    for (int e = 0; e < 125; ++e) {
+      const int q[3] = {e % 5, (e / 5) % 5, e / 25};
+      int child = 0, local[3];
+      for (int d = 0; d < 3; ++d) {  // classes 0, 1 in the lower child, 2, 3, 4 its nodes 0, inner, k of the upper
+        if (q[d] >= 2) child |= 1 << d;
+        local[d] = q[d] >= 2 ? q[d] - 2 : q[d];
+      }
+      T.refined_fdesc[g * transfer_record(5) + e] =
+          record(T.refined_fine[child * nrg + g], slot3(local[0], local[1], local[2]));
+    }
+    coarse_record(T.refined_cdesc, g, T.refined_coarse[g]);
+  }
+  for (int64_t e = 0; e < fine.n_entities; ++e)
+    MFMG_REQUIRE(!wanted[e] || claimed[e] || fine.ent_size[e] == 0, MFMG_ERR_INVALID_ARG,
                  "transfer entity without an owner");
   return T;
 }

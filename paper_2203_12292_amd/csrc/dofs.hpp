@@ -117,19 +117,18 @@ LevelDofs build_level_dofs(const Octree& tree, int k, bool dirichlet, bool codes
 // Transfer data between a fine level and the next coarser one (Section 3.5).
 // Geometric: every coarse cell is a fine cell (identity category) or the
 // parent of 8 fine cells (refinement category).  Polynomial: same cells,
-// one category.  valence[slot][fine cell] = number of transfer groups (coarse
-// cells) in which the slot's entity appears unconstrained; 0 for constrained
-// (hanging or Dirichlet) slots.  The prolongation weights are 1/valence.
+// one category.
 struct TransferDofs {
   bool polynomial = false;
   std::vector<int32_t> ident_coarse, ident_fine;   // identity category pairs
   std::vector<int32_t> refined_coarse;             // refinement category coarse cells
   std::vector<int32_t> refined_fine;               // [8][n_refined] children, child c = sx + 2 sy + 4 sz
-  // [N_SLOTS][n_fine_cells]: number of groups in which the entity appears
-  // unconstrained (0: constrained or Dirichlet), plus TRANSFER_OWNER on the
-  // one (fine cell, slot) pair that writes (prolongation) or reads
-  // (restriction) the entity
-  std::vector<uint8_t> valence;
+  // one record per group (transfer_record in slots.hpp): the first DoF of the
+  // lattice entities that the group writes (prolongation) or reads
+  // (restriction); -1 for constrained entities and those another group owns.
+  // The coarse records: the first DoFs of the coarse cell's entities, then its
+  // mask.
+  std::vector<int32_t> ident_fdesc, refined_fdesc, ident_cdesc, refined_cdesc;
   // with `coloured`: both group lists in colour order (no two groups of a
   // colour share a coarse entity) and the colour ranges
   std::vector<int64_t> ident_off, refined_off;

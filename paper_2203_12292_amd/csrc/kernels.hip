@@ -16,8 +16,7 @@
 // are 1D interpolations along the lines of the hanging faces/edges, applied
 // in the phase whose lines run along that axis: gather + z, y, x before the
 // operator, transposed z, x, y after it, then the scatter.
-#include "common.hpp"
-#include "fe1d.hpp"
+#include "device.hpp"
 #include "geometry.hpp"
 #include "kernels.hpp"
 #include "slots.hpp"
@@ -63,24 +62,12 @@ struct OpTab2 {
   T Hg[2 * N * N];  // [s][i][j] = l_j((s + xi_i)/2)
 };
 
-template <typename T, int NF, int NC>
-struct TrTab {
-  T P[NF * NC];     // 1D prolongation, row-major NF x NC
-  T H[2][NC * NC];  // hanging interpolation of the coarse cell
-};
-
 template <int N>
 struct Gauss1D {
   double x[N];      // Gauss points on [0, 1]
   double w[N];      // weights
   double S[N * N];  // S[q*N + i] = l_i(x_q)
 };
-
-inline const Tables1D& tables(int k) {
-  static Tables1D t[7] = {Tables1D(1), Tables1D(1), Tables1D(2), Tables1D(3),
-                          Tables1D(4), Tables1D(5), Tables1D(6)};
-  return t[k];
-}
 
 template <int N>
 Gauss1D<N> make_gauss() {
@@ -300,37 +287,6 @@ __device__ __forceinline__ void interp(const T (&H)[2][N * N], int s, T (&u)[N])
   for (int i = 0; i < N; ++i) u[i] = out[i];
 }
 
-template <typename T> __device__ __forceinline__ void atomic_add(T* p, T v) { unsafeAtomicAdd(p, v); }
-
-// bfloat16 add through a compare-and-swap on the enclosing 32-bit word
-// (used only on the small levels stored in bfloat16)
-__device__ __forceinline__ void atomic_add_bf16(bf16* p, float v) {
-  uintptr_t addr = reinterpret_cast<uintptr_t>(p);
-  unsigned int* word = reinterpret_cast<unsigned int*>(addr & ~uintptr_t(3));
-  const unsigned int shift = (addr & 2) ? 16u : 0u;
-  unsigned int old = *word, assumed;
-  do {
-    assumed = old;
-    bf16 cur;
-    cur.bits = static_cast<uint16_t>((assumed >> shift) & 0xffffu);
-    bf16 nv = float_to_bf16(bf16_to_float(cur) + v);
-    unsigned int repl = (assumed & ~(0xffffu << shift)) | (static_cast<unsigned int>(nv.bits) << shift);
-    old = atomicCAS(word, assumed, repl);
-  } while (old != assumed);
-}
-
-// dst += v for a storage-typed vector entry; `exclusive` entries have no
-// concurrent writer and use a plain read-modify-write.
-template <typename S, typename T>
-__device__ __forceinline__ void add_to(S* p, T v, bool exclusive) {
-  if (exclusive) {
-    *p = store_as<S>(load_as<T>(*p) + v);
-  } else {
-    if constexpr (sizeof(S) == 2) atomic_add_bf16(reinterpret_cast<bf16*>(p), static_cast<float>(v));
-    else atomic_add(p, static_cast<S>(v));
-  }
-}
-
 // scatter-add of the line of nodes (a, 0..k, c) (along y); cell interiors are
 // owned by the cell (plain store), shared entities use atomics.
 // `plain`: no other cell writes the same entities concurrently (deterministic
@@ -367,17 +323,6 @@ __device__ __forceinline__ void scatter_yline(const int32_t* __restrict__ ent, i
     }
   }
 }
-
-// Barrier of the cell pipeline.  All lanes of a cell belong to one
-// wavefront and LDS operations of a wavefront execute in order, so a compiler
-// code-motion barrier with wavefront-scope fences is enough.
-struct WaveSync {
-  __device__ __forceinline__ void operator()() const {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-};
 
 // The cell pipeline C^T S^T Q S C on the block's LDS.  Input: this thread's
 // z-line (x = ta, y = tb) of gathered slot values.  Output: this thread's
@@ -1504,224 +1449,6 @@ __global__ void __launch_bounds__((K + 1) * (K + 1))
   scatter_yline<K>(ent, nc, cell, ta, tb, u, b, nv, v, cells != nullptr);
 }
 
-}  // namespace mfmg
-
-namespace mfmg {
-
-// ---------------------------------------------------------------------------
-// Intergrid transfer (Section 3.5, Eq. eq:impl:loop:categorized): one coarse
-// cell (transfer group) per block.  Prolongation:
-//   coarse gather G_c with constraints C_c (in-place interpolation),
-//   category prolongation P (three 1D sweeps; identity category: none),
-//   weights W, scatter S_f.
-// Restriction is the transpose of every step.  The weights: the paper's W
-// divides each fine value by the number of groups that reach it, so that the
-// groups' equal contributions sum to it once.  Here W is 1 on one owner
-// (fine cell, slot) pair per fine entity and 0 elsewhere (and on constrained
-// fine DoFs): the same operator, and the prolongation writes each fine DoF
-// from one block with a plain read-modify-write instead of atomics.
-//
-// Lattice of a group: NF nodes per axis.  Refinement category: NF = 2k+1
-// nodes covering the 8 children (child along an axis = node index >= k);
-// polynomial category: NF = k_f+1; identity: NF = NC, no sweeps.
-//
-// Several interleaved vectors are handled VB at a time: the vector index is
-// the fastest one of the threads and of the LDS arrays ([node][VB]), so the
-// VB values of a DoF, adjacent in memory, are read and written by adjacent
-// threads.  VB is the largest power of two <= 8 whose arrays fit 32 KB.
-constexpr int TR_THREADS = 256;
-
-template <int NF, int NC, typename T>
-constexpr int transfer_vb() {
-  constexpr int per = (NC * NC * NC + NF * NC * NC + NF * NF * NC + NF * NF * NF) * static_cast<int>(sizeof(T));
-  return per * 8 <= 32768 ? 8 : per * 4 <= 32768 ? 4 : per * 2 <= 32768 ? 2 : 1;
-}
-
-// in-place hanging-node interpolation of the coarse cell's node values
-// X[node][VB] (vectors vv < nb)
-template <int KC, int VB, typename T>
-__device__ __forceinline__ void constraints_lds(T* X, uint32_t m, const T (&H)[2][(KC + 1) * (KC + 1)],
-                                                bool trans, int nb) {
-  constexpr int N = KC + 1, N2 = N * N;
-  for (int d = 0; d < 3; ++d) {
-    __syncthreads();
-    const int s = mask_sub(m, d);
-    for (int t = threadIdx.x; t < N2 * nb; t += blockDim.x) {
-      const int line = t / nb, vv = t - line * nb;
-      const int p = line % N, q = line / N;
-      if (!hanging_line(m, d, p, q, KC)) continue;
-      T u[N];
-      const int stride = d == 0 ? 1 : d == 1 ? N : N2;
-      const int base = d == 0 ? p * N + q * N2 : d == 1 ? p + q * N2 : p + q * N;
-#pragma unroll
-      for (int r = 0; r < N; ++r) u[r] = X[(base + r * stride) * VB + vv];
-      if (trans) interp<N, T, true>(H, s, u);
-      else interp<N, T, false>(H, s, u);
-#pragma unroll
-      for (int r = 0; r < N; ++r) X[(base + r * stride) * VB + vv] = u[r];
-    }
-  }
-  __syncthreads();
-}
-
-// out (NO along axis d) = P (NO x NI) applied along axis d of `in`; the
-// other two axes (in increasing order) have extents na, nb in both; layout x
-// fastest, then the VB vectors innermost
-template <int NI, int NO, int VB, typename T, bool TRANS>
-__device__ __forceinline__ void sweep_lds(const T* in, T* out, const T* __restrict__ P, int d, int na, int nb,
-                                          int nvb) {
-  const int lines = na * nb;
-  for (int t = threadIdx.x; t < lines * nvb; t += blockDim.x) {
-    const int line = t / nvb, vv = t - line * nvb;
-    const int p = line % na, q = line / na;
-    int sin, sout, bin, bout;
-    if (d == 0) { sin = 1; sout = 1; bin = (p + q * na) * NI; bout = (p + q * na) * NO; }
-    else if (d == 1) { sin = na; sout = na; bin = p + q * na * NI; bout = p + q * na * NO; }
-    else { sin = na * nb; sout = na * nb; bin = p + q * na; bout = p + q * na; }
-    T u[NI];
-#pragma unroll
-    for (int r = 0; r < NI; ++r) u[r] = in[(bin + r * sin) * VB + vv];
-#pragma unroll
-    for (int i = 0; i < NO; ++i) {
-      T acc = T(0);
-#pragma unroll
-      for (int j = 0; j < NI; ++j) acc += (TRANS ? P[j * NO + i] : P[i * NI + j]) * u[j];
-      out[(bout + i * sout) * VB + vv] = acc;
-    }
-  }
-}
-
-// fine lattice node I (per axis) -> (child bit, local node)
-template <int KF, int NF>
-__device__ __forceinline__ void lattice_local(int I, int& child, int& a) {
-  if constexpr (NF == 2 * KF + 1) {
-    child = I >= KF ? 1 : 0;
-    a = I - child * KF;
-  } else {
-    child = 0;
-    a = I;
-  }
-}
-
-template <int KF, int KC, int NF, typename S, typename T>
-__global__ void __launch_bounds__(TR_THREADS)
-    prolongate_kernel(const int32_t* __restrict__ fent, int64_t nfc, const int32_t* __restrict__ cent,
-                      const uint32_t* __restrict__ cmask, int64_t ncc, const int32_t* __restrict__ group_coarse,
-                      const int32_t* __restrict__ group_fine, int64_t gstride, int nchild,
-                      const uint8_t* __restrict__ valence, TrTab<T, NF, KC + 1> tab, const S* __restrict__ src,
-                      S* __restrict__ dst, int nv) {
-  constexpr int NC = KC + 1, NC3 = NC * NC * NC, NF3 = NF * NF * NF;
-  constexpr bool IDENT = (NF == NC) && (KF == KC);
-  constexpr int VB = transfer_vb<NF, NC, T>();
-  __shared__ T X[NC3 * VB];
-  __shared__ T Y1[IDENT ? 1 : NF * NC * NC * VB];
-  __shared__ T Y2[IDENT ? 1 : NF * NF * NC * VB];
-  __shared__ T Y3[IDENT ? 1 : NF3 * VB];
-  const int64_t g = blockIdx.x;
-  const int64_t cc = group_coarse[g];
-  const uint32_t mc = cmask[cc];
-  for (int v0 = 0; v0 < nv; v0 += VB) {
-    const int nb = nv - v0 < VB ? nv - v0 : VB;
-    if (v0 > 0) __syncthreads();
-    for (int t = threadIdx.x; t < NC3 * nb; t += blockDim.x) {
-      const int i = t / nb, vv = t - i * nb;
-      const int a = i % NC, b = (i / NC) % NC, c = i / (NC * NC);
-      const int s = node_slot(a, b, c, KC);
-      const int32_t e = cent[s * ncc + cc];
-      X[i * VB + vv] =
-          e < 0 ? T(0) : load_as<T>(src[static_cast<int64_t>(e + node_offset(a, b, c, KC)) * nv + v0 + vv]);
-    }
-    if (mask_hanging(mc)) constraints_lds<KC, VB, T>(X, mc, tab.H, false, nb);
-    else __syncthreads();
-    const T* Y = X;
-    if constexpr (!IDENT) {
-      sweep_lds<NC, NF, VB, T, false>(X, Y1, tab.P, 0, NC, NC, nb);
-      __syncthreads();
-      sweep_lds<NC, NF, VB, T, false>(Y1, Y2, tab.P, 1, NF, NC, nb);
-      __syncthreads();
-      sweep_lds<NC, NF, VB, T, false>(Y2, Y3, tab.P, 2, NF, NF, nb);
-      __syncthreads();
-      Y = Y3;
-    }
-    for (int t = threadIdx.x; t < NF3 * nb; t += blockDim.x) {
-      const int i = t / nb, vv = t - i * nb;
-      const int I = i % NF, J = (i / NF) % NF, L = i / (NF * NF);
-      int cx, cy, cz, a, b, c;
-      lattice_local<KF, NF>(I, cx, a);
-      lattice_local<KF, NF>(J, cy, b);
-      lattice_local<KF, NF>(L, cz, c);
-      const int child = nchild == 8 ? cx + 2 * cy + 4 * cz : 0;
-      const int64_t f = group_fine[child * gstride + g];
-      const int s = node_slot(a, b, c, KF);
-      // one (cell, slot) pair owns each fine entity: a plain read-modify-write
-      if (!(valence[s * nfc + f] & TRANSFER_OWNER)) continue;
-      const int32_t e = fent[s * nfc + f];
-      const int64_t idx = static_cast<int64_t>(e + node_offset(a, b, c, KF)) * nv + v0 + vv;
-      add_to<S, T>(&dst[idx], Y[i * VB + vv], true);
-    }
-  }
-}
-
-template <int KF, int KC, int NF, typename S, typename T>
-__global__ void __launch_bounds__(TR_THREADS)
-    restrict_kernel(const int32_t* __restrict__ fent, int64_t nfc, const int32_t* __restrict__ cent,
-                    const uint32_t* __restrict__ cmask, int64_t ncc, const int32_t* __restrict__ group_coarse,
-                    const int32_t* __restrict__ group_fine, int64_t gstride, int nchild,
-                    const uint8_t* __restrict__ valence, TrTab<T, NF, KC + 1> tab, const S* __restrict__ src,
-                    S* __restrict__ dst, int nv, bool plain) {
-  constexpr int NC = KC + 1, NC3 = NC * NC * NC, NF3 = NF * NF * NF;
-  constexpr bool IDENT = (NF == NC) && (KF == KC);
-  constexpr int VB = transfer_vb<NF, NC, T>();
-  __shared__ T X[NC3 * VB];
-  __shared__ T Y1[IDENT ? 1 : NF * NC * NC * VB];
-  __shared__ T Y2[IDENT ? 1 : NF * NF * NC * VB];
-  __shared__ T Y3[IDENT ? 1 : NF3 * VB];
-  const int64_t g = blockIdx.x;
-  const int64_t cc = group_coarse[g];
-  const uint32_t mc = cmask[cc];
-  for (int v0 = 0; v0 < nv; v0 += VB) {
-    const int nb = nv - v0 < VB ? nv - v0 : VB;
-    if (v0 > 0) __syncthreads();
-    T* Yw = IDENT ? X : Y3;
-    for (int t = threadIdx.x; t < NF3 * nb; t += blockDim.x) {
-      const int i = t / nb, vv = t - i * nb;
-      const int I = i % NF, J = (i / NF) % NF, L = i / (NF * NF);
-      int cx, cy, cz, a, b, c;
-      lattice_local<KF, NF>(I, cx, a);
-      lattice_local<KF, NF>(J, cy, b);
-      lattice_local<KF, NF>(L, cz, c);
-      const int child = nchild == 8 ? cx + 2 * cy + 4 * cz : 0;
-      const int64_t f = group_fine[child * gstride + g];
-      const int s = node_slot(a, b, c, KF);
-      T y = T(0);
-      if (valence[s * nfc + f] & TRANSFER_OWNER) {  // each fine value enters once
-        const int32_t e = fent[s * nfc + f];
-        y = load_as<T>(src[static_cast<int64_t>(e + node_offset(a, b, c, KF)) * nv + v0 + vv]);
-      }
-      Yw[i * VB + vv] = y;
-    }
-    __syncthreads();
-    if constexpr (!IDENT) {
-      sweep_lds<NF, NC, VB, T, true>(Y3, Y2, tab.P, 2, NF, NF, nb);
-      __syncthreads();
-      sweep_lds<NF, NC, VB, T, true>(Y2, Y1, tab.P, 1, NF, NC, nb);
-      __syncthreads();
-      sweep_lds<NF, NC, VB, T, true>(Y1, X, tab.P, 0, NC, NC, nb);
-      __syncthreads();
-    }
-    if (mask_hanging(mc)) constraints_lds<KC, VB, T>(X, mc, tab.H, true, nb);
-    for (int t = threadIdx.x; t < NC3 * nb; t += blockDim.x) {
-      const int i = t / nb, vv = t - i * nb;
-      const int a = i % NC, b = (i / NC) % NC, c = i / (NC * NC);
-      const int s = node_slot(a, b, c, KC);
-      const int32_t e = cent[s * ncc + cc];
-      if (e < 0) continue;
-      add_to<S, T>(&dst[static_cast<int64_t>(e + node_offset(a, b, c, KC)) * nv + v0 + vv], X[i * VB + vv],
-                   plain || s == 26);
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // vector kernels
 constexpr int VEC_THREADS = 256;
@@ -1927,11 +1654,6 @@ __global__ void cg_p_kernel(int64_t n_dofs, int nv, const double* __restrict__ n
 // host launchers
 namespace {
 
-void check_launch() {
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) throw Error(MFMG_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
-}
-
 void zero_bytes(void* p, int64_t bytes, hipStream_t s) {
   if (bytes <= 0) return;
   if (bytes % 4 == 0 && reinterpret_cast<uintptr_t>(p) % 4 == 0) {
@@ -2127,121 +1849,6 @@ void rhs_k(const CellView& c, int kind, const double* params, int n_terms, int n
   });
 }
 
-template <typename T, int NF, int NC>
-TrTab<T, NF, NC> make_trtab(int kf, int kc) {
-  TrTab<T, NF, NC> t;
-  const Tables1D& tc = tables(kc);
-  for (int i = 0; i < NC * NC; ++i) {
-    t.H[0][i] = static_cast<T>(tc.H[0][i]);
-    t.H[1][i] = static_cast<T>(tc.H[1][i]);
-  }
-  if (kf == kc && NF == 2 * kc + 1) {
-    for (int i = 0; i < NF * NC; ++i) t.P[i] = static_cast<T>(tc.T[i]);
-  } else if (kf != kc && NF == 2 * kf + 1) {
-    std::vector<double> P = hp_transfer_matrix(kf, kc);
-    for (int i = 0; i < NF * NC; ++i) t.P[i] = static_cast<T>(P[i]);
-  } else if (kf != kc) {
-    std::vector<double> P = p_transfer_matrix(kf, kc);
-    for (int i = 0; i < NF * NC; ++i) t.P[i] = static_cast<T>(P[i]);
-  } else {
-    for (int i = 0; i < NF * NC; ++i) t.P[i] = static_cast<T>((i / NC) == (i % NC) ? 1.0 : 0.0);
-  }
-  return t;
-}
-
-template <int KF, int KC, int NF, typename S>
-void transfer_launch(bool prolong, const CellView& f, const CellView& c, const TransferView& t,
-                     const int32_t* gc, const int32_t* gf, int64_t ng, int nchild, int nv, void* dst,
-                     const void* src, hipStream_t s) {
-  using T = typename Acc<S>::type;
-  if (ng == 0) return;
-  static const TrTab<T, NF, KC + 1> tab = make_trtab<T, NF, KC + 1>(KF, KC);
-  if (prolong) {  // each fine DoF has one writer: no colouring needed
-    prolongate_kernel<KF, KC, NF, S, T><<<static_cast<unsigned>(ng), TR_THREADS, 0, s>>>(
-        f.ent, f.n_cells, c.ent, c.mask, c.n_cells, gc, gf, ng, nchild, t.valence, tab,
-        static_cast<const S*>(src), static_cast<S*>(dst), nv);
-    check_launch();
-    return;
-  }
-  // restriction: one launch, or in the deterministic mode one per colour of
-  // the group list (plain adds into the coarse DoFs)
-  const int64_t* off = nchild == 1 ? t.ident_off : t.refined_off;
-  const int n_col = nchild == 1 ? t.n_ident_colors : t.n_refined_colors;
-  const int64_t whole[2] = {0, ng};
-  const bool det = t.deterministic && off != nullptr;
-  const int64_t* o = det ? off : whole;
-  for (int k = 0; k < (det ? n_col : 1); ++k) {
-    const int64_t n = o[k + 1] - o[k];
-    if (n == 0) continue;
-    restrict_kernel<KF, KC, NF, S, T><<<static_cast<unsigned>(n), TR_THREADS, 0, s>>>(
-        f.ent, f.n_cells, c.ent, c.mask, c.n_cells, gc + o[k], gf + o[k], ng, nchild, t.valence, tab,
-        static_cast<const S*>(src), static_cast<S*>(dst), nv, det);
-    check_launch();
-  }
-}
-
-template <int K, typename S>
-void transfer_h(bool prolong, const CellView& f, const CellView& c, const TransferView& t, int nv, void* dst,
-                const void* src, hipStream_t s) {
-  transfer_launch<K, K, K + 1, S>(prolong, f, c, t, t.ident_coarse, t.ident_fine, t.n_ident, 1, nv, dst, src, s);
-  transfer_launch<K, K, 2 * K + 1, S>(prolong, f, c, t, t.refined_coarse, t.refined_fine, t.n_refined, 8, nv,
-                                     dst, src, s);
-}
-
-// geometric and polynomial coarsening in one step: identity pairs change the
-// degree only, refined groups change both
-template <int KF, int KC, typename S>
-void transfer_hp(bool prolong, const CellView& f, const CellView& c, const TransferView& t, int nv, void* dst,
-                 const void* src, hipStream_t s) {
-  transfer_launch<KF, KC, KF + 1, S>(prolong, f, c, t, t.ident_coarse, t.ident_fine, t.n_ident, 1, nv, dst, src, s);
-  transfer_launch<KF, KC, 2 * KF + 1, S>(prolong, f, c, t, t.refined_coarse, t.refined_fine, t.n_refined, 8, nv,
-                                         dst, src, s);
-}
-
-template <typename S>
-void transfer_s(bool prolong, const CellView& f, const CellView& c, const TransferView& t, int nv, void* dst,
-                const void* src, hipStream_t s) {
-  if (!t.polynomial && f.k != c.k) {
-    switch (f.k * 10 + c.k) {
-      case 21: transfer_hp<2, 1, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 31: transfer_hp<3, 1, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 42: transfer_hp<4, 2, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 52: transfer_hp<5, 2, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 63: transfer_hp<6, 3, S>(prolong, f, c, t, nv, dst, src, s); break;
-      default: throw Error(MFMG_ERR_UNSUPPORTED, "combined h and p transfer pair");
-    }
-    return;
-  }
-  if (!t.polynomial) {
-    switch (f.k) {
-      case 1: transfer_h<1, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 2: transfer_h<2, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 3: transfer_h<3, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 4: transfer_h<4, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 5: transfer_h<5, S>(prolong, f, c, t, nv, dst, src, s); break;
-      case 6: transfer_h<6, S>(prolong, f, c, t, nv, dst, src, s); break;
-      default: throw Error(MFMG_ERR_UNSUPPORTED, "degree");
-    }
-    return;
-  }
-  const int key = f.k * 10 + c.k;
-  switch (key) {
-#define MFMG_P(KF, KC)                                                                                  \
-  case KF * 10 + KC:                                                                                   \
-    transfer_launch<KF, KC, KF + 1, S>(prolong, f, c, t, t.ident_coarse, t.ident_fine, t.n_ident, 1, nv, dst, \
-                                       src, s);                                                        \
-    break;
-    MFMG_P(2, 1)
-    MFMG_P(3, 1)
-    MFMG_P(4, 2)
-    MFMG_P(5, 2)
-    MFMG_P(6, 3)
-#undef MFMG_P
-    default:
-      throw Error(MFMG_ERR_UNSUPPORTED, "polynomial transfer pair");
-  }
-}
-
 }  // namespace
 
 void launch_vmult_fused(const CellView& c, int dtype, int nv, void* dst, const void* src, const FusedStep& f,
@@ -2301,26 +1908,6 @@ void launch_rhs(const CellView& c, int kind, const double* params, int n_terms, 
     case 5: rhs_k<5>(c, kind, params, n_terms, nv, b, s); break;
     case 6: rhs_k<6>(c, kind, params, n_terms, nv, b, s); break;
     default: throw Error(MFMG_ERR_UNSUPPORTED, "degree");
-  }
-}
-
-void launch_prolongate(const CellView& f, const CellView& c, const TransferView& t, int dtype, int nv, void* dst,
-                       const void* src, hipStream_t s) {
-  switch (dtype) {
-    case MFMG_F64: transfer_s<double>(true, f, c, t, nv, dst, src, s); break;
-    case MFMG_F32: transfer_s<float>(true, f, c, t, nv, dst, src, s); break;
-    case MFMG_BF16: transfer_s<bf16>(true, f, c, t, nv, dst, src, s); break;
-    default: throw Error(MFMG_ERR_UNSUPPORTED, "dtype");
-  }
-}
-
-void launch_restrict(const CellView& f, const CellView& c, const TransferView& t, int dtype, int nv, void* dst,
-                     const void* src, hipStream_t s) {
-  switch (dtype) {
-    case MFMG_F64: transfer_s<double>(false, f, c, t, nv, dst, src, s); break;
-    case MFMG_F32: transfer_s<float>(false, f, c, t, nv, dst, src, s); break;
-    case MFMG_BF16: transfer_s<bf16>(false, f, c, t, nv, dst, src, s); break;
-    default: throw Error(MFMG_ERR_UNSUPPORTED, "dtype");
   }
 }
 

@@ -77,7 +77,12 @@ struct TransferView {
   const int32_t* refined_coarse = nullptr;
   const int32_t* refined_fine = nullptr;  // [8][n_refined]
   int64_t n_refined = 0;
-  const uint8_t* valence = nullptr;       // [27][n_fine_cells]
+  // per group one record each (transfer_record): the first DoF of every
+  // entity of its fine lattice that it owns (-1: constrained, Dirichlet or
+  // another group's), and the first DoFs of its coarse cell's entities (-1
+  // Dirichlet) with the coarse cell's mask at index 27
+  const int32_t *ident_fdesc = nullptr, *refined_fdesc = nullptr;
+  const int32_t *ident_cdesc = nullptr, *refined_cdesc = nullptr;
   // deterministic mode: the restriction runs the groups colour by colour (no
   // two groups of a colour share a coarse entity, plain adds); the group
   // lists are in colour order and ident_off / refined_off (host, colours + 1)

@@ -118,8 +118,11 @@ __host__ __device__ inline float mask_coef(uint32_t m) {
   return __builtin_bit_cast(float, bits);
 }
 constexpr uint32_t MASK_COEF_BITS = 0xff00fe00u;
-// transfer valence byte: owner flag (the low bits count the groups)
-constexpr uint8_t TRANSFER_OWNER = 0x80;
+// Records of the transfer groups: a lattice with `classes` node classes per
+// axis (3: one cell; 5: the eight children of a refined cell) has classes^3
+// entities, numbered x fastest; the record is padded to a multiple of 4
+// integers (a coarse cell's record holds its mask behind the 27 entities).
+__host__ __device__ constexpr int transfer_record(int classes) { return (classes * classes * classes + 3) / 4 * 4; }
 // The mask bits of a coefficient c in [1e-30, 1e30]: c rounded to 8
 // significant bits (bfloat16), ties to even, from the bits of the double.
 __host__ __device__ inline uint32_t coef_bits(double c) {

@@ -297,7 +297,10 @@ void init_transfer(Level& L, const TransferDofs& T, bool poly) {
   L.tr_ident_f.upload(T.ident_fine);
   L.tr_ref_c.upload(T.refined_coarse);
   L.tr_ref_f.upload(T.refined_fine);
-  L.tr_valence.upload(T.valence);
+  L.tr_ident_fdesc.upload(T.ident_fdesc);
+  L.tr_ident_cdesc.upload(T.ident_cdesc);
+  L.tr_ref_fdesc.upload(T.refined_fdesc);
+  L.tr_ref_cdesc.upload(T.refined_cdesc);
   L.tview.polynomial = poly;
   L.tview.ident_coarse = L.tr_ident_c.ptr;
   L.tview.ident_fine = L.tr_ident_f.ptr;
@@ -305,7 +308,10 @@ void init_transfer(Level& L, const TransferDofs& T, bool poly) {
   L.tview.refined_coarse = L.tr_ref_c.ptr;
   L.tview.refined_fine = L.tr_ref_f.ptr;
   L.tview.n_refined = static_cast<int64_t>(T.refined_coarse.size());
-  L.tview.valence = L.tr_valence.ptr;
+  L.tview.ident_fdesc = L.tr_ident_fdesc.ptr;
+  L.tview.ident_cdesc = L.tr_ident_cdesc.ptr;
+  L.tview.refined_fdesc = L.tr_ref_fdesc.ptr;
+  L.tview.refined_cdesc = L.tr_ref_cdesc.ptr;
 }
 
 int level_dtype(const mfmg_level_desc& desc, int l) {
