@@ -882,6 +882,7 @@ __global__ void __launch_bounds__(BATCH_WAVES * 64)
   struct Pre {
     int g0, g1, gm, s0, s1, sm;
     uint32_t mask;
+    int lev;  // of the record read (its cell's own, also on lanes without a cell: it indexes the geometry table)
   };
 
   if constexpr ((FK & FUSE_ATOMIC) != 0) nv = 1;  // (one vector: the index arithmetic folds)
@@ -949,7 +950,8 @@ __global__ void __launch_bounds__(BATCH_WAVES * 64)
       uint32_t sl = slots;
       asm volatile("" : "+v"(sl));  // (keeps the unpacking here, not hoisted out of the loops)
       Pre p{L[sl & 31u],         L[(sl >> 5) & 31u],  L[(sl >> 10) & 31u],
-            L[(sl >> 15) & 31u], L[(sl >> 20) & 31u], L[sl >> 25],         M->mask};
+            L[(sl >> 15) & 31u], L[(sl >> 20) & 31u], L[sl >> 25],         M->mask, 0};
+      p.lev = mask_level(p.mask);
       p.g0 = ok ? p.g0 : ZB;
       p.g1 = ok ? p.g1 : ZB;
       p.gm = ok ? p.gm : ZB;
@@ -991,7 +993,7 @@ __global__ void __launch_bounds__(BATCH_WAVES * 64)
       bool zline = true;
       if constexpr (GEO != 0) {  // mapped cell: its own map from its coarse cell
         const int64_t cell = (lane_used && cw + lc < c1) ? cw + lc : c0;
-        const CellGeo<T> g = cell_geo<T>(geo, ijk, cell, mask_level(mk), n0);
+        const CellGeo<T> g = cell_geo<T>(geo, ijk, cell, cur.lev, n0);
         cell_pipeline_mapped<K, T, WaveSync>(B0, mk, wave_hang, static_cast<T>(mask_coef(mk)), mt, g, Hg, ta, tb, u);
       } else {
         zline = cell_pipeline_zfirst<K, T, WaveSync, UNI>(B0, mk, wave_hang, h, tab, Hg, ta, tb, u);
