@@ -38,7 +38,8 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "vmult_q4_cube16_ball4_hbm_traffic.md")
 # sources that determine the operator kernels, their metadata and their compilation
 OPERATOR_SOURCES = [os.path.join("paper_2203_12292_amd", "csrc", f) for f in
-                    ("kernels.hip", "kernels.hpp", "slots.hpp", "dofs.cpp", "dofs.hpp", "fe1d.hpp", "common.hpp")]
+                    ("vmult.hpp", "vmult_f64.hip", "eig.hpp", "mapped.hpp", "geometry.hpp", "device.hpp", "kernels.hpp",
+                     "slots.hpp", "solver.cpp", "dofs.cpp", "dofs.hpp", "fe1d.hpp", "common.hpp")]
 OPERATOR_SOURCES.append(os.path.join("paper_2203_12292_amd", "build.py"))
 
 

@@ -59,4 +59,13 @@ struct WaveSync {
   }
 };
 
+constexpr int VEC_THREADS = 256;
+
+inline unsigned grid_for(int64_t n, int per_thread = 1) {
+  int64_t b = (n + static_cast<int64_t>(VEC_THREADS) * per_thread - 1) / (static_cast<int64_t>(VEC_THREADS) * per_thread);
+  if (b < 1) b = 1;
+  if (b > 1 << 20) b = 1 << 20;
+  return static_cast<unsigned>(b);
+}
+
 }  // namespace mfmg

@@ -1,24 +1,15 @@
-// Device kernels of the matrix-free multigrid hot path (CDNA4 / gfx950).
+// Set-up kernels (diagonal, load vector, constraint distribution, coefficient),
+// vector kernels and the pieces of the outer CG (CDNA4 / gfx950).
 //
-// Cell operator (Eq. impl:mf): v = sum_e G_e^T C_e^T S_e^T Q_e S_e C_e G_e x.
-// Every cell is an axis-aligned cube of side h, so the quadrature-point
-// operation Q_e reduces to the scalar h * w_q and the cell matrix has the
-// tensor form h (K (x) M (x) M + M (x) K (x) M + M (x) M (x) K) with the 1D
-// mass M and stiffness K integrated exactly by the (k+1)-point Gauss rule.
-// The kernel applies it as seven 1D sweeps: M_x/K_x, then M_y/K_y, then
-// M_z/K_z (fewer contractions than interpolating to quadrature points and
-// back, same result up to rounding).
-//
-// Thread layout: n^2 threads per cell (n = k+1), each owning one line of n
-// nodes; a block holds CPB cells.  A phase works on lines along one axis in
-// registers; LDS re-distributes the cell's n^3 values between phases.
-// Hanging-node constraints (Section 3.2, the in-place interpolation variant)
-// are 1D interpolations along the lines of the hanging faces/edges, applied
-// in the phase whose lines run along that axis: gather + z, y, x before the
-// operator, transposed z, x, y after it, then the scatter.
+// The cell kernels here take n^2 threads per cell (n = k+1), each owning one
+// line of n nodes: a phase works on lines along one axis in registers; LDS
+// re-distributes the cell's n^3 values between phases.  Hanging-node
+// constraints (Section 3.2, the in-place interpolation variant) are 1D
+// interpolations along the lines of the hanging faces/edges, applied in the
+// phase whose lines run along that axis.
 #include "device.hpp"
-#include "geometry.hpp"
 #include "kernels.hpp"
+#include "mapped.hpp"
 #include "slots.hpp"
 
 namespace mfmg {
@@ -32,35 +23,18 @@ struct OpTab {
   T H[2][N * N];
 };
 
-// A symmetric, centrosymmetric n x n matrix (the 1D mass and stiffness
-// matrices on Gauss-Lobatto nodes) in even-odd form: with h = n/2,
-// e_j = x_j + x_{n-1-j}, o_j = x_j - x_{n-1-j} (j < h),
-//   y_i       = sum_j E_ij e_j + c_i x_h + sum_j O_ij o_j      (i < h)
-//   y_{n-1-i} = sum_j E_ij e_j + c_i x_h - sum_j O_ij o_j
-//   y_h       = sum_j c_j e_j + d x_h                          (n odd)
-// where E = (A_ij + A_i,n-1-j)/2 and O = (A_ij - A_i,n-1-j)/2 are symmetric
-// (upper triangles stored), c_i = A_ih, d = A_hh.
 template <typename T, int N>
-struct SymMat {
-  static constexpr int H = N / 2;
-  static constexpr int NE = H * (H + 1) / 2;
-  T e[NE > 0 ? NE : 1];
-  T o[NE > 0 ? NE : 1];
-  T c[H > 0 ? H : 1];
-  T d;
-};
-
-__host__ __device__ constexpr int sym_idx(int i, int j, int h) {
-  return i <= j ? i * h - i * (i - 1) / 2 + (j - i) : j * h - j * (j - 1) / 2 + (i - j);
+OpTab<T, N> make_optab() {
+  const Tables1D& t = tables(N - 1);
+  OpTab<T, N> o;
+  for (int i = 0; i < N * N; ++i) {
+    o.M[i] = static_cast<T>(t.M[i]);
+    o.K[i] = static_cast<T>(t.K[i]);
+    o.H[0][i] = static_cast<T>(t.H[0][i]);
+    o.H[1][i] = static_cast<T>(t.H[1][i]);
+  }
+  return o;
 }
-
-// Operator tables: mass and stiffness in even-odd form (kernel arguments,
-// scalar registers) and the hanging-node interpolation (copied to LDS).
-template <typename T, int N>
-struct OpTab2 {
-  SymMat<T, N> M, K;
-  T Hg[2 * N * N];  // [s][i][j] = l_j((s + xi_i)/2)
-};
 
 template <int N>
 struct Gauss1D {
@@ -79,165 +53,6 @@ Gauss1D<N> make_gauss() {
   }
   for (int i = 0; i < N * N; ++i) g.S[i] = t.S[i];
   return g;
-}
-
-template <typename T, int N>
-OpTab<T, N> make_optab() {
-  const Tables1D& t = tables(N - 1);
-  OpTab<T, N> o;
-  for (int i = 0; i < N * N; ++i) {
-    o.M[i] = static_cast<T>(t.M[i]);
-    o.K[i] = static_cast<T>(t.K[i]);
-    o.H[0][i] = static_cast<T>(t.H[0][i]);
-    o.H[1][i] = static_cast<T>(t.H[1][i]);
-  }
-  return o;
-}
-
-template <typename T, int N>
-SymMat<T, N> make_sym(const std::vector<double>& A) {
-  SymMat<T, N> m{};
-  constexpr int H = N / 2;
-  for (int i = 0; i < H; ++i)
-    for (int j = i; j < H; ++j) {
-      m.e[sym_idx(i, j, H)] = static_cast<T>(0.5 * (A[i * N + j] + A[i * N + (N - 1 - j)]));
-      m.o[sym_idx(i, j, H)] = static_cast<T>(0.5 * (A[i * N + j] - A[i * N + (N - 1 - j)]));
-    }
-  if (N % 2) {
-    for (int i = 0; i < H; ++i) m.c[i] = static_cast<T>(A[i * N + H]);
-    m.d = static_cast<T>(A[H * N + H]);
-  }
-  return m;
-}
-
-template <typename T, int N>
-OpTab2<T, N> make_optab2() {
-  const Tables1D& t = tables(N - 1);
-  OpTab2<T, N> o;
-  o.M = make_sym<T, N>(t.M);
-  o.K = make_sym<T, N>(t.K);
-  for (int i = 0; i < N * N; ++i) {
-    o.Hg[i] = static_cast<T>(t.H[0][i]);
-    o.Hg[N * N + i] = static_cast<T>(t.H[1][i]);
-  }
-  return o;
-}
-
-// The hanging interpolation matrices of both halves in constant memory, for
-// wavefronts holding one cell: read with uniform addresses, they become
-// scalar loads and scalar operands.  Filled once per device before the first
-// operator launch that uses them.
-template <typename T, int N>
-struct HgTable {
-  T v[2 * N * N];
-};
-template <typename T, int N>
-__constant__ HgTable<T, N> kHgTab;
-
-template <typename T, int N>
-void ensure_hg_table() {
-  static bool done[64] = {};
-  int dev = 0;
-  MFMG_HIP(hipGetDevice(&dev));
-  MFMG_REQUIRE(dev >= 0 && dev < 64, MFMG_ERR_UNSUPPORTED, "device index");
-  if (done[dev]) return;
-  const OpTab2<T, N> o = make_optab2<T, N>();
-  MFMG_HIP(hipMemcpyToSymbol(HIP_SYMBOL((kHgTab<T, N>)), o.Hg, sizeof(o.Hg)));
-  done[dev] = true;
-}
-
-// y = A x for a SymMat A (even-odd evaluation)
-template <int N, typename T>
-__device__ __forceinline__ void sym_mv(const SymMat<T, N>& A, const T (&x)[N], T (&y)[N]) {
-  constexpr int H = N / 2;
-  T e[H > 0 ? H : 1], o[H > 0 ? H : 1];
-#pragma unroll
-  for (int j = 0; j < H; ++j) {
-    e[j] = x[j] + x[N - 1 - j];
-    o[j] = x[j] - x[N - 1 - j];
-  }
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    T se = A.e[sym_idx(i, 0, H)] * e[0];
-    T so = A.o[sym_idx(i, 0, H)] * o[0];
-#pragma unroll
-    for (int j = 1; j < H; ++j) {
-      se += A.e[sym_idx(i, j, H)] * e[j];
-      so += A.o[sym_idx(i, j, H)] * o[j];
-    }
-    if constexpr (N % 2 == 1) se += A.c[i] * x[H];
-    y[i] = se + so;
-    y[N - 1 - i] = se - so;
-  }
-  if constexpr (N % 2 == 1) {
-    T m = A.d * x[H];
-#pragma unroll
-    for (int j = 0; j < H; ++j) m += A.c[j] * e[j];
-    y[H] = m;
-  }
-}
-
-// In-place hanging interpolation of a line from the LDS table Hg (both
-// halves, [s][i][j]): u <- H_s u (H_s^T u if TRANS).
-template <int N, typename T, bool TRANS>
-__device__ __forceinline__ void interp_lds(const T* __restrict__ Hg, int s, T (&u)[N]) {
-  const T* Hs = Hg + s * N * N;
-  T out[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    T acc = T(0);
-#pragma unroll
-    for (int j = 0; j < N; ++j) acc += Hs[TRANS ? j * N + i : i * N + j] * u[j];
-    out[i] = acc;
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) u[i] = out[i];
-}
-
-// The same from the constant-memory table when s is the same on every lane
-// of the wavefront (one cell per wavefront): the branch is uniform and the
-// table entries are scalar operands, no LDS reads.
-template <int N, typename T, bool TRANS, int S>
-__device__ __forceinline__ void interp_const(T (&u)[N]) {
-  // an opaque copy of the table address keeps the loads here, next to their
-  // use (hoisted out of the cell loop, 2 x N^2 values would not fit the
-  // scalar registers)
-  using CT = const __attribute__((address_space(4))) T;
-  CT* tbl = reinterpret_cast<CT*>(reinterpret_cast<uintptr_t>(kHgTab<T, N>.v)) + S * N * N;
-  asm volatile("" : "+s"(tbl));
-  T out[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    T acc = T(0);
-#pragma unroll
-    for (int j = 0; j < N; ++j) acc += tbl[TRANS ? j * N + i : i * N + j] * u[j];
-    out[i] = acc;
-  }
-#pragma unroll
-  for (int i = 0; i < N; ++i) u[i] = out[i];
-}
-
-// u <- H_s u (H_s^T u if TRANS) for the hanging lines of a cell, from the
-// constant-memory table.  UNI: s is wavefront-uniform, a uniform branch picks
-// the half.  Otherwise s differs between the cells of a wavefront: the halves
-// are mirror images, H_1 = J H_0 J with J the reversal of the node order (the
-// nodes are symmetric about the midpoint and l_j(1 - t) = l_{n-1-j}(t)), so
-// each lane reverses its line where s = 1, applies H_0 (scalar operands) and
-// reverses back: 2n selects instead of n^2 LDS reads of the table.
-template <int N, typename T, bool TRANS, bool UNI>
-__device__ __forceinline__ void hang_interp(const T* __restrict__ Hg, int s, T (&u)[N]) {
-  (void)Hg;
-  if constexpr (UNI) {
-    if (s) interp_const<N, T, TRANS, 1>(u);
-    else interp_const<N, T, TRANS, 0>(u);
-  } else {
-    T w[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) w[j] = s ? u[N - 1 - j] : u[j];
-    interp_const<N, T, TRANS, 0>(w);
-#pragma unroll
-    for (int i = 0; i < N; ++i) u[i] = s ? w[N - 1 - i] : w[i];
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -419,691 +234,6 @@ __device__ __forceinline__ void cell_pipeline(T* __restrict__ B0, T* __restrict_
   }
 }
 
-// The cell pipeline with even-odd 1D operators, z-sweeps first:
-//   a = M_z u, b = K_z u;  c = M_y a, f = K_y a + M_y b;  out = h (K_x c + M_x f),
-// which is h (K_x M_y M_z + M_x K_y M_z + M_x M_y K_z) u.  Input: this lane's
-// z-line (x = ta, y = tb) of gathered values, so the z-sweeps start from
-// registers.  In a wavefront without hanging nodes the result is this lane's
-// x-line (y = ta, z = tb) and the function returns false.  Otherwise the
-// interpolations of the hanging lines (they commute with each other) are
-// applied around the sweeps: z in registers and y, x through LDS before,
-// x in registers and y, z through LDS after; the result is then this lane's
-// z-line (the gather layout) and the function returns true.  Hg (LDS) holds
-// the interpolation matrices of both halves.  UNI: the wavefront holds one
-// cell and m is wavefront-uniform (the interpolation then reads its matrices
-// from the kernel arguments).  Must be called by all lanes of the wavefront.
-template <int K, typename T, typename Sync, bool UNI = false>
-__device__ __forceinline__ bool cell_pipeline_zfirst(T* __restrict__ B0, uint32_t m,
-                                                     int any_hang, T h, const OpTab2<T, K + 1>& tab,
-                                                     const T* __restrict__ Hg, int ta, int tb, T (&u)[K + 1]) {
-  constexpr int N = K + 1, N2 = N * N;
-  const Sync sync{};
-  const bool hang = mask_hanging(m);
-  if (any_hang) {
-    if (hang && hanging_line(m, 2, ta, tb, K)) hang_interp<N, T, false, UNI>(Hg, mask_sub(m, 2), u);
-#pragma unroll
-    for (int c = 0; c < N; ++c) B0[c * N2 + tb * N + ta] = u[c];
-    sync();
-    if (hang && hanging_line(m, 1, ta, tb, K)) {
-#pragma unroll
-      for (int r = 0; r < N; ++r) u[r] = B0[tb * N2 + r * N + ta];
-      hang_interp<N, T, false, UNI>(Hg, mask_sub(m, 1), u);
-#pragma unroll
-      for (int r = 0; r < N; ++r) B0[tb * N2 + r * N + ta] = u[r];
-    }
-    sync();
-    if (hang && hanging_line(m, 0, ta, tb, K)) {
-#pragma unroll
-      for (int r = 0; r < N; ++r) u[r] = B0[tb * N2 + ta * N + r];
-      hang_interp<N, T, false, UNI>(Hg, mask_sub(m, 0), u);
-#pragma unroll
-      for (int r = 0; r < N; ++r) B0[tb * N2 + ta * N + r] = u[r];
-    }
-    sync();
-#pragma unroll
-    for (int c = 0; c < N; ++c) u[c] = B0[c * N2 + tb * N + ta];  // own z-line, rewritten below
-  }
-  // One n^3 buffer per cell carries the four transposes one after the
-  // other: a (z-lines -> y-lines), b (z -> y), c (y -> x), f (y -> x).  The
-  // lanes of a cell are one wavefront, whose LDS operations execute in
-  // order, so a buffer may be rewritten as soon as the previous read of it
-  // has been issued; Sync keeps the compiler from reordering across.
-  // Ordered to keep few values live: a dies into c and f once read back
-  // along y, then b adds M_y b to f, and so on.
-  T a[N], b[N], c[N], f[N];
-  sym_mv<N>(tab.M, u, a);
-  sym_mv<N>(tab.K, u, b);
-#pragma unroll
-  for (int q = 0; q < N; ++q) B0[q * N2 + tb * N + ta] = a[q];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) a[r] = B0[tb * N2 + r * N + ta];
-  sym_mv<N>(tab.M, a, c);
-  sym_mv<N>(tab.K, a, f);
-  sync();
-#pragma unroll
-  for (int q = 0; q < N; ++q) B0[q * N2 + tb * N + ta] = b[q];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) a[r] = B0[tb * N2 + r * N + ta];
-  sym_mv<N>(tab.M, a, b);
-#pragma unroll
-  for (int r = 0; r < N; ++r) f[r] += b[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B0[tb * N2 + r * N + ta] = c[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) a[r] = B0[tb * N2 + ta * N + r];
-  sym_mv<N>(tab.K, a, c);
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B0[tb * N2 + r * N + ta] = f[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) a[r] = B0[tb * N2 + ta * N + r];
-  sym_mv<N>(tab.M, a, b);
-#pragma unroll
-  for (int r = 0; r < N; ++r) u[r] = h * (c[r] + b[r]);
-  if (!any_hang) return false;
-  if (hang && hanging_line(m, 0, ta, tb, K)) hang_interp<N, T, true, UNI>(Hg, mask_sub(m, 0), u);
-#pragma unroll
-  for (int r = 0; r < N; ++r) B0[tb * N2 + ta * N + r] = u[r];  // this lane's own x-line
-  sync();
-  if (hang && hanging_line(m, 1, ta, tb, K)) {
-#pragma unroll
-    for (int r = 0; r < N; ++r) u[r] = B0[tb * N2 + r * N + ta];
-    hang_interp<N, T, true, UNI>(Hg, mask_sub(m, 1), u);
-#pragma unroll
-    for (int r = 0; r < N; ++r) B0[tb * N2 + r * N + ta] = u[r];
-  }
-  sync();
-#pragma unroll
-  for (int c = 0; c < N; ++c) u[c] = B0[c * N2 + tb * N + ta];
-  if (hang && hanging_line(m, 2, ta, tb, K)) hang_interp<N, T, true, UNI>(Hg, mask_sub(m, 2), u);
-  return true;
-}
-
-// Per-lane constants of the operator kernel, for lane t = ta + n tb of a
-// cell: entity slot and in-entity offsets (first node, first interior node,
-// stride between interior nodes) of the lane's z-line (x = ta, y = tb) and
-// x-line (y = ta, z = tb).  Built at compile time, read once per wavefront.
-struct LaneLines {
-  uint8_t zs0, zs1, zsm, zo0, zom, zst;
-  uint8_t xs0, xs1, xsm, xo0, xom, xst;
-};
-template <int K>
-struct LaneLineTable {
-  LaneLines t[(K + 1) * (K + 1)];
-};
-template <int K>
-constexpr LaneLineTable<K> make_lane_lines() {
-  LaneLineTable<K> r{};
-  for (int tb = 0; tb <= K; ++tb)
-    for (int ta = 0; ta <= K; ++ta) {
-      LaneLines& l = r.t[ta + (K + 1) * tb];
-      l.zs0 = static_cast<uint8_t>(node_slot(ta, tb, 0, K));
-      l.zs1 = static_cast<uint8_t>(node_slot(ta, tb, K, K));
-      l.zsm = static_cast<uint8_t>(K > 1 ? node_slot(ta, tb, 1, K) : 26);
-      l.zo0 = static_cast<uint8_t>(node_offset(ta, tb, 0, K));
-      l.zom = static_cast<uint8_t>(K > 1 ? node_offset(ta, tb, 1, K) : 0);
-      l.zst = static_cast<uint8_t>(K > 2 ? node_offset(ta, tb, 2, K) - node_offset(ta, tb, 1, K) : 0);
-      l.xs0 = static_cast<uint8_t>(node_slot(0, ta, tb, K));
-      l.xs1 = static_cast<uint8_t>(node_slot(K, ta, tb, K));
-      l.xsm = static_cast<uint8_t>(K > 1 ? node_slot(1, ta, tb, K) : 26);
-      l.xo0 = static_cast<uint8_t>(node_offset(0, ta, tb, K));
-      l.xom = static_cast<uint8_t>(K > 1 ? node_offset(1, ta, tb, K) : 0);
-      l.xst = static_cast<uint8_t>(K > 2 ? node_offset(2, ta, tb, K) - node_offset(1, ta, tb, K) : 0);
-    }
-  return r;
-}
-template <int K>
-__constant__ LaneLineTable<K> kLaneLines = make_lane_lines<K>();
-
-// Gauss-point tables of the operator on mapped cells: S[q][i] = l_i(g_q)
-// (Gauss-Lobatto basis at the Gauss points), D[q][p] = L_p'(g_q) (derivative
-// of the Lagrange basis on the Gauss points: gradients from point values),
-// the Gauss points g and weights w on [0, 1].
-template <typename T, int N>
-struct MapTab {
-  T S[N * N];
-  T D[N * N];
-  T g[N];
-  T w[N];
-};
-
-template <typename T, int N>
-MapTab<T, N> make_maptab() {
-  const Tables1D& t = tables(N - 1);
-  MapTab<T, N> m;
-  for (int q = 0; q < N; ++q) {
-    m.g[q] = static_cast<T>(t.qp[q]);
-    m.w[q] = static_cast<T>(t.qw[q]);
-    for (int i = 0; i < N; ++i) {
-      m.S[q * N + i] = static_cast<T>(t.S[q * N + i]);
-      m.D[q * N + i] = static_cast<T>(lagrange_deriv(t.qp, i, t.qp[q]));
-    }
-  }
-  return m;
-}
-
-// y = A x (TRANS: y = A^T x) for an n x n table A
-template <int N, typename T, bool TRANS>
-__device__ __forceinline__ void mat_mv(const T* __restrict__ A, const T (&x)[N], T (&y)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    T acc = (TRANS ? A[i] : A[i * N]) * x[0];
-#pragma unroll
-    for (int j = 1; j < N; ++j) acc += (TRANS ? A[j * N + i] : A[i * N + j]) * x[j];
-    y[i] = acc;
-  }
-}
-
-// Geometry of one cell of a mapped level: the coarse cell's map coefficients
-// (monomial form, see geometry.hpp) and the cell's box inside it,
-// t = (r + xi) * scale.
-template <typename T>
-struct CellGeo {
-  const T* A;
-  T r[3];
-  T scale;
-};
-
-// The cell pipeline C^T S^T Q S C on a mapped cell (Eq. impl:mf with the
-// general Q_e): values at the Gauss points by three sweeps of S, reference
-// gradients at the points by sweeps of D, the metric term
-// c_e w_q |det J| J^{-1} J^{-T} at every point (J from the cell's trilinear
-// map), the transposed sweeps D^T and S^T.  The one n^3 buffer B of the cell
-// re-distributes the values between the line directions.  Input: this lane's
-// z-line (x = ta, y = tb) of gathered slot values; output: the same z-line
-// of the result (the gather layout).  Hanging lines are interpolated as in
-// the axis-aligned pipeline (before: z in registers, y and x in LDS; after:
-// the transposes, z in registers, y and x in LDS).  Must be called by all
-// lanes of the wavefront.
-template <int K, typename T, typename Sync>
-__device__ __forceinline__ void cell_pipeline_mapped(T* __restrict__ B, uint32_t m, int any_hang, T coef,
-                                                     const MapTab<T, K + 1>& mt, const CellGeo<T>& geo,
-                                                     const T* __restrict__ Hg, int ta, int tb, T (&u)[K + 1]) {
-  constexpr int N = K + 1, N2 = N * N;
-  const Sync sync{};
-  const bool hang = mask_hanging(m);
-  auto zl = [&](int c) { return c * N2 + tb * N + ta; };  // z-line (x = ta, y = tb)
-  auto yl = [&](int r) { return tb * N2 + r * N + ta; };  // y-line (x = ta, z = tb)
-  auto xl = [&](int r) { return tb * N2 + ta * N + r; };  // x-line (y = ta, z = tb)
-  if (any_hang) {
-    if (hang && hanging_line(m, 2, ta, tb, K)) interp_lds<N, T, false>(Hg, mask_sub(m, 2), u);
-#pragma unroll
-    for (int c = 0; c < N; ++c) B[zl(c)] = u[c];
-    sync();
-    if (hang && hanging_line(m, 1, ta, tb, K)) {
-#pragma unroll
-      for (int r = 0; r < N; ++r) u[r] = B[yl(r)];
-      interp_lds<N, T, false>(Hg, mask_sub(m, 1), u);
-#pragma unroll
-      for (int r = 0; r < N; ++r) B[yl(r)] = u[r];
-    }
-    sync();
-    if (hang && hanging_line(m, 0, ta, tb, K)) {
-#pragma unroll
-      for (int r = 0; r < N; ++r) u[r] = B[xl(r)];
-      interp_lds<N, T, false>(Hg, mask_sub(m, 0), u);
-#pragma unroll
-      for (int r = 0; r < N; ++r) B[xl(r)] = u[r];
-    }
-    sync();
-#pragma unroll
-    for (int c = 0; c < N; ++c) u[c] = B[zl(c)];
-    sync();
-  }
-  T v[N], w[N], gx[N], gy[N], gz[N];
-  // values at the Gauss points: z, y, x
-  mat_mv<N, T, false>(mt.S, u, v);
-#pragma unroll
-  for (int c = 0; c < N; ++c) B[zl(c)] = v[c];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) w[r] = B[yl(r)];
-  mat_mv<N, T, false>(mt.S, w, v);
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[yl(r)] = v[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) w[r] = B[xl(r)];
-  mat_mv<N, T, false>(mt.S, w, v);
-  mat_mv<N, T, false>(mt.D, v, gx);  // d/dxi_1 along this x-line
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[xl(r)] = v[r];
-  sync();
-  // d/dxi_2 (y-lines) and d/dxi_3 (z-lines), brought to this lane's x-line
-#pragma unroll
-  for (int r = 0; r < N; ++r) w[r] = B[yl(r)];
-#pragma unroll
-  for (int r = 0; r < N; ++r) v[r] = B[zl(r)];
-  mat_mv<N, T, false>(mt.D, w, gy);
-  mat_mv<N, T, false>(mt.D, v, gz);
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[yl(r)] = gy[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) gy[r] = B[xl(r)];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[zl(r)] = gz[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) gz[r] = B[xl(r)];
-  // quadrature points (x = r, y = ta, z = tb): flux G grad u
-  {
-    const T t2 = (geo.r[1] + mt.g[ta]) * geo.scale, t3 = (geo.r[2] + mt.g[tb]) * geo.scale;
-    const T wyz = mt.w[ta] * mt.w[tb] * coef;
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-      const T t1 = (geo.r[0] + mt.g[r]) * geo.scale;
-      T J[3][3];
-      geo_jacobian<T>(geo.A, t1, t2, t3, J);
-#pragma unroll
-      for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int e = 0; e < 3; ++e) J[d][e] *= geo.scale;
-      T G[6];
-      geo_metric<T>(J, wyz * mt.w[r], G);
-      const T a = gx[r], b = gy[r], c = gz[r];
-      gx[r] = G[0] * a + G[1] * b + G[2] * c;
-      gy[r] = G[1] * a + G[3] * b + G[4] * c;
-      gz[r] = G[2] * a + G[4] * b + G[5] * c;
-    }
-  }
-  // transposed gradient sweeps, summed along this lane's x-line
-  mat_mv<N, T, true>(mt.D, gx, v);
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[xl(r)] = gy[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) w[r] = B[yl(r)];
-  mat_mv<N, T, true>(mt.D, w, gy);
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[yl(r)] = gy[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) v[r] += B[xl(r)];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[xl(r)] = gz[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) w[r] = B[zl(r)];
-  mat_mv<N, T, true>(mt.D, w, gz);
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[zl(r)] = gz[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) v[r] += B[xl(r)];
-  // back to the nodes: S^T along x, y, z
-  mat_mv<N, T, true>(mt.S, v, w);
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[xl(r)] = w[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) v[r] = B[yl(r)];
-  mat_mv<N, T, true>(mt.S, v, w);
-#pragma unroll
-  for (int r = 0; r < N; ++r) B[yl(r)] = w[r];
-  sync();
-#pragma unroll
-  for (int r = 0; r < N; ++r) v[r] = B[zl(r)];
-  mat_mv<N, T, true>(mt.S, v, u);
-  if (!any_hang) return;
-  if (hang && hanging_line(m, 2, ta, tb, K)) interp_lds<N, T, true>(Hg, mask_sub(m, 2), u);
-  sync();
-#pragma unroll
-  for (int c = 0; c < N; ++c) B[zl(c)] = u[c];
-  sync();
-  if (hang && hanging_line(m, 1, ta, tb, K)) {
-#pragma unroll
-    for (int r = 0; r < N; ++r) w[r] = B[yl(r)];
-    interp_lds<N, T, true>(Hg, mask_sub(m, 1), w);
-#pragma unroll
-    for (int r = 0; r < N; ++r) B[yl(r)] = w[r];
-  }
-  sync();
-  if (hang && hanging_line(m, 0, ta, tb, K)) {
-#pragma unroll
-    for (int r = 0; r < N; ++r) w[r] = B[xl(r)];
-    interp_lds<N, T, true>(Hg, mask_sub(m, 0), w);
-#pragma unroll
-    for (int r = 0; r < N; ++r) B[xl(r)] = w[r];
-  }
-  sync();
-#pragma unroll
-  for (int c = 0; c < N; ++c) u[c] = B[zl(c)];
-}
-
-// geometry of cell `cell` of a mapped level (its lattice position ijk and
-// level l; the coarse grid has n0 cells per axis)
-template <typename T>
-__device__ __forceinline__ CellGeo<T> cell_geo(const T* __restrict__ table, const int32_t* __restrict__ ijk,
-                                               int64_t cell, int l, int n0) {
-  CellGeo<T> g;
-  const int i = ijk[3 * cell], j = ijk[3 * cell + 1], k = ijk[3 * cell + 2];
-  const int I = i >> l, J = j >> l, Kc = k >> l;
-  g.A = table + (static_cast<int64_t>(I) + n0 * (J + static_cast<int64_t>(n0) * Kc)) * 24;
-  g.r[0] = static_cast<T>(i - (I << l));
-  g.r[1] = static_cast<T>(j - (J << l));
-  g.r[2] = static_cast<T>(k - (Kc << l));
-  g.scale = static_cast<T>(ldexp(1.0, -l));
-  return g;
-}
-
-// Shared-DoF route of the batch kernel, or-ed into the fused kind by the
-// launcher: the shared DoFs' sums are added with global atomics (into dst for
-// the plain operator, else into an accumulator that finish_shared_kernel
-// completes) instead of being written as partial sums
-constexpr int FUSE_ATOMIC = 4;
-constexpr int base_kind(int fk) { return fk & 3; }
-
-// Final value t = (A x) of DoF g, vector v, and the fused step applied to it
-template <typename S, typename T, int FK>
-__device__ __forceinline__ void finish_dof(const FusedStep& f, int64_t g, int nv, int v, T t, T* __restrict__ dst) {
-  const int64_t e = g * nv + v;
-  if constexpr (base_kind(FK) == FUSE_NONE) {
-    dst[e] = t;
-  } else if constexpr (base_kind(FK) == FUSE_RESIDUAL) {
-    static_cast<S*>(f.r)[e] = store_as<S>(load_as<T>(static_cast<const S*>(f.b)[e]) - t);
-  } else {
-    S* d = static_cast<S*>(f.d);
-    S* x = static_cast<S*>(f.x);
-    const T di = static_cast<const T*>(f.dinv)[g];
-    const T dd = f.c_dd != 0.0 ? static_cast<T>(f.c_dd) * load_as<T>(d[e]) : T(0);
-    const T dn = dd + static_cast<T>(f.c_r) * di * (load_as<T>(static_cast<const S*>(f.b)[e]) - t);
-    x[e] = store_as<S>(load_as<T>(x[e]) + dn);
-    d[e] = store_as<S>(dn);
-  }
-}
-
-// Operator evaluation by cell batches.  The blocks are persistent: the
-// batches are split into 8 contiguous ranges, one per XCD (block i runs on XCD
-// i mod 8), and the blocks of an XCD take the batches of its range in turn,
-// so neighbouring batches share that XCD's L2.  Per batch, the batch's DoFs
-// are loaded into LDS (shared DoFs through their index list, exclusive DoFs as
-// one contiguous range), the cells are evaluated group by group from LDS and
-// their contributions accumulated in LDS, then the exclusive DoFs are stored
-// contiguously and the shared DoFs either added with global atomics
-// (FUSE_ATOMIC route, one vector: into dst, or into the accumulator in the
-// partial buffer when a step is fused; either cleared before) or written as
-// this batch's partial sums (reduced afterwards).  gridDim.x is a multiple
-// of 8.
-// register budget: 4 wavefronts per SIMD (two blocks per CU, as the LDS
-// allows); the operator of mapped cells, which holds three gradient
-// components and the metric terms of a line of points, gets the registers of
-// 2 wavefronts per SIMD instead of spilling
-template <int K, int FK, int GEO>
-struct BatchWavesPerEu {
-  static constexpr int value = GEO ? 2 : 4;
-};
-
-template <int K, typename S, typename T, int FK, int GEO, bool DET>
-__global__ void __launch_bounds__(BATCH_WAVES * 64)
-    __attribute__((amdgpu_waves_per_eu(BatchWavesPerEu<K, FK, GEO>::value)))
-    vmult_batch_kernel(const CellMeta* __restrict__ meta, const int32_t* __restrict__ bcell,
-                       const int32_t* __restrict__ bsh, const int32_t* __restrict__ bex,
-                       const int32_t* __restrict__ sh_idx, int64_t nb,
-                       int64_t n_shared, double h0, OpTab2<T, K + 1> tab, const S* __restrict__ src,
-                       T* __restrict__ partial, T* __restrict__ dst, int nv, FusedStep fs,
-                       const T* __restrict__ geo, const int32_t* __restrict__ ijk, int n0, MapTab<T, K + 1> mt) {
-  constexpr int N = K + 1, N2 = N * N, N3 = N2 * N, CPW = cells_per_wave(N), MCAP = batch_mcap(K);
-  constexpr int NZ = batch_zero_entries(K), ZB = MCAP;  // zero block behind the batch's DoFs
-  constexpr int BT = BATCH_WAVES * 64, PER = (MCAP + BT - 1) / BT;
-  __shared__ T in_[MCAP + NZ];
-  __shared__ double out_[MCAP + NZ];  // contributions accumulate in FP64 (also for FP32 arithmetic)
-  __shared__ T Hg[2 * N2];
-  constexpr bool META_LDS = batch_meta_in_lds(K);
-  __shared__ CellMeta metaL[META_LDS ? batch_max_cells(K) : 1];
-  __shared__ T buf0[(BATCH_WAVES * CPW + 1) * N3];
-  for (int i = threadIdx.x; i < NZ; i += BT) in_[ZB + i] = T(0);
-  for (int i = threadIdx.x; i < 2 * N2; i += BT) Hg[i] = tab.Hg[i];
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int lc = lane / N2;
-  const int t = lane - lc * N2;
-  const bool lane_used = lc < CPW;
-  const int ta = t % N, tb = t / N;
-  // lanes without a cell work on the block's spare buffers (results unused)
-  T* B0 = buf0 + (lane_used ? wave * CPW + lc : BATCH_WAVES * CPW) * N3;
-  const LaneLines ll = kLaneLines<K>.t[t];
-  const int gsm = ll.zsm, go0 = ll.zo0, gom = ll.zom, gst = ll.zst;
-  const int ssm = ll.xsm, so0 = ll.xo0, som = ll.xom, sst = ll.xst;
-  // the six slots of the lane's z-line and x-line (each < 27), five bits
-  // apiece: the metadata fetch unpacks them each time instead of holding six
-  // 64-bit offsets through the batch loop
-  const uint32_t slots = ll.zs0 | (ll.zs1 << 5) | (ll.zsm << 10) | (ll.xs0 << 15) | (ll.xs1 << 20) |
-                         (static_cast<uint32_t>(ll.xsm) << 25);
-  struct Pre {
-    int g0, g1, gm, s0, s1, sm;
-    uint32_t mask;
-    int lev;  // of the record read (its cell's own, also on lanes without a cell: it indexes the geometry table)
-  };
-
-  if constexpr ((FK & FUSE_ATOMIC) != 0) nv = 1;  // (one vector: the index arithmetic folds)
-  const int64_t per = (nb + 7) / 8;
-  const int64_t lo = (blockIdx.x % 8) * per;
-  const int64_t hi = lo + per < nb ? lo + per : nb;
-  // several interleaved vectors: nv blocks of one XCD (consecutive block
-  // indices there) take the same batch at the same time, one vector each,
-  // so that the nv values of a DoF, adjacent in memory, are read once into
-  // that XCD's L2 and their partial-line writes meet there.  (Vectors one
-  // after the other in one block left a whole pass of the other blocks'
-  // traffic between two passes over a line, so that it was fetched and
-  // written back up to nv times.)  The launch gives every XCD at least nv
-  // blocks.
-  const int groups = static_cast<int>(gridDim.x / 8) / nv;
-  const int j = static_cast<int>(blockIdx.x / 8);
-  if (j >= groups * nv) return;  // (whole block: no barrier passed yet)
-  const int v = j % nv;
-  const int64_t b0 = lo + j / nv;
-  for (int64_t w = 0;; ++w) {
-    const int64_t b = b0 + w * groups;
-    if (b >= hi) break;
-    const int c0 = bcell[b], c1 = bcell[b + 1];
-    const int sh0 = bsh[b], nsh = bsh[b + 1] - sh0;
-    const int64_t ex0 = n_shared + bex[b];
-    const int m = nsh + (bex[b + 1] - bex[b]);
-    // stage the batch's DoFs: all index loads of a thread, then all value
-    // loads, then the LDS stores, so that the loads of a thread overlap
-    {
-      int32_t gi[PER];  // DoF indices (a level has fewer than 2^31 DoFs)
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int i = threadIdx.x + q * BT;
-        gi[q] = i < nsh ? sh_idx[sh0 + i] : static_cast<int32_t>(ex0 + (i - nsh));
-      }
-      T val[PER];
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int i = threadIdx.x + q * BT;
-        val[q] = i < m ? load_as<T>(src[static_cast<int64_t>(gi[q]) * nv + v]) : T(0);
-      }
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int i = threadIdx.x + q * BT;
-        if (i < m) {
-          in_[i] = val[q];
-          out_[i] = 0.0;
-        }
-      }
-    }
-    // metadata of this lane's cell, fetched one cell group ahead: the six
-    // local entity starts of its z-line and x-line and the mask (the loads are
-    // unconditional, from the batch's first cell for lanes without a cell, so
-    // that the wait for them can be counted exactly; such lanes then point at
-    // the zero block)
-    if constexpr (META_LDS) {  // the batch's cell records, 16 bytes per thread
-      const uint4* gsrc = reinterpret_cast<const uint4*>(meta + c0);
-      uint4* ldst = reinterpret_cast<uint4*>(metaL);
-      for (int i = threadIdx.x; i < (c1 - c0) * 4; i += BT) ldst[i] = gsrc[i];
-    }
-    auto fetch = [&](int64_t cell) {
-      const bool ok = lane_used && cell < c1;
-      const CellMeta* M = META_LDS ? metaL + (ok ? cell - c0 : 0) : meta + (ok ? cell : c0);
-      const uint16_t* L = M->loc;
-      uint32_t sl = slots;
-      asm volatile("" : "+v"(sl));  // (keeps the unpacking here, not hoisted out of the loops)
-      Pre p{L[sl & 31u],         L[(sl >> 5) & 31u],  L[(sl >> 10) & 31u],
-            L[(sl >> 15) & 31u], L[(sl >> 20) & 31u], L[sl >> 25],         M->mask, 0};
-      p.lev = mask_level(p.mask);
-      p.g0 = ok ? p.g0 : ZB;
-      p.g1 = ok ? p.g1 : ZB;
-      p.gm = ok ? p.gm : ZB;
-      p.s0 = ok ? p.s0 : ZB;
-      p.s1 = ok ? p.s1 : ZB;
-      p.sm = ok ? p.sm : ZB;
-      p.mask = ok ? p.mask : 0u;
-      return p;
-    };
-    int cw = c0 + wave * CPW;
-    if constexpr (META_LDS) __syncthreads();
-    Pre nx = fetch(cw + lc);
-    if constexpr (!META_LDS) __syncthreads();
-    // deterministic mode: every wavefront runs the same number of rounds (the
-    // last one partly without cells), and the scatter below goes one cell at
-    // a time in cell order
-    const int rounds = DET ? (c1 - c0 + BATCH_WAVES * CPW - 1) / (BATCH_WAVES * CPW) : 0;
-    for (int round = 0;; ++round, cw += BATCH_WAVES * CPW) {
-      if constexpr (DET) {
-        if (round >= rounds) break;
-      } else {
-        if (cw >= c1) break;
-      }
-      const Pre cur = nx;
-      nx = fetch(cw + BATCH_WAVES * CPW + lc);
-      // one cell per wavefront: its mask is uniform (lanes without a cell
-      // take it too; their results are discarded)
-      constexpr bool UNI = CPW == 1 && GEO == 0;
-      const uint32_t mk = UNI ? __builtin_amdgcn_readfirstlane(cur.mask) : cur.mask;
-      const int wave_hang = UNI ? (mask_hanging(mk) ? 1 : 0) : __any(mask_hanging(mk) ? 1 : 0);
-      const T h = static_cast<T>(ldexp(h0, -mask_level(mk)) * static_cast<double>(mask_coef(mk)));
-      T u[N];
-      u[0] = in_[cur.g0 + go0];
-      u[K] = in_[cur.g1 + go0];
-      if constexpr (K > 1) {
-#pragma unroll
-        for (int c = 1; c < K; ++c) u[c] = in_[cur.gm + gom + (c - 1) * gst];
-      }
-      bool zline = true;
-      if constexpr (GEO != 0) {  // mapped cell: its own map from its coarse cell
-        const int64_t cell = (lane_used && cw + lc < c1) ? cw + lc : c0;
-        const CellGeo<T> g = cell_geo<T>(geo, ijk, cell, cur.lev, n0);
-        cell_pipeline_mapped<K, T, WaveSync>(B0, mk, wave_hang, static_cast<T>(mask_coef(mk)), mt, g, Hg, ta, tb, u);
-      } else {
-        zline = cell_pipeline_zfirst<K, T, WaveSync, UNI>(B0, mk, wave_hang, h, tab, Hg, ta, tb, u);
-      }
-      // scatter-add along the result line, skipping absent entities and
-      // lanes without a cell (they point at the zero block); a line through
-      // the cell interior (slot 26) holds DoFs of this cell only
-      const int s0 = zline ? cur.g0 : cur.s0, s1 = zline ? cur.g1 : cur.s1, sm = zline ? cur.gm : cur.sm;
-      const int o0 = zline ? go0 : so0, om = zline ? gom : som, st = zline ? gst : sst;
-      auto add = [&](int i, T v) {
-        if constexpr (DET) out_[i] += static_cast<double>(v);  // the only writer at this moment
-        else atomicAdd(&out_[i], static_cast<double>(v));
-      };
-      auto scatter = [&]() {
-        if (s0 < ZB) add(s0 + o0, u[0]);
-        if (s1 < ZB) add(s1 + o0, u[K]);
-        if constexpr (K > 1) {
-          if (sm < ZB) {
-            if ((zline ? gsm : ssm) == 26) {
-#pragma unroll
-              for (int r = 1; r < K; ++r) out_[sm + om + (r - 1) * st] = static_cast<double>(u[r]);
-            } else {
-#pragma unroll
-              for (int r = 1; r < K; ++r) add(sm + om + (r - 1) * st, u[r]);
-            }
-          }
-        }
-      };
-      if constexpr (DET) {
-        for (int q = 0; q < BATCH_WAVES * CPW; ++q) {  // cell c0 + round * (block's cells) + q
-          if (lane_used && wave * CPW + lc == q) scatter();
-          __syncthreads();
-        }
-      } else {
-        scatter();
-      }
-      WaveSync{}();  // the next cell group reuses this wavefront's buffers
-    }
-    // write back: the shared DoFs' sums atomically into dst or the
-    // accumulator (their indices read again: keeping them in registers
-    // through the evaluation would spill) or as one contiguous range of
-    // partial sums (the batch's part of the partial buffer); exclusive DoFs
-    // in place, with the fused step
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      const int i = threadIdx.x + q * BT;
-      if (i < nsh) {
-        if constexpr ((FK & FUSE_ATOMIC) != 0)
-          unsafeAtomicAdd(&(base_kind(FK) == FUSE_NONE ? dst : partial)[sh_idx[sh0 + i]], static_cast<T>(out_[i]));
-        else partial[static_cast<int64_t>(sh0 + i) * nv + v] = static_cast<T>(out_[i]);
-      } else if (i < m) finish_dof<S, T, FK>(fs, ex0 + (i - nsh), nv, v, static_cast<T>(out_[i]), dst);
-    }
-    __syncthreads();  // the next batch or vector overwrites in_ and out_
-  }
-}
-
-template <typename T>
-__global__ void clear_shared_kernel(int64_t n, T* __restrict__ dst) {
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    dst[i] = T(0);
-}
-
-// the fused step on the shared DoFs of one vector, from their sums (A x)_s
-// accumulated atomically in acc
-template <typename S, typename T, int FK>
-__global__ void finish_shared_kernel(int64_t n_shared, const T* __restrict__ acc, T* __restrict__ dst, FusedStep fs) {
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n_shared;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    finish_dof<S, T, FK>(fs, i, 1, 0, acc[i], dst);
-}
-
-// (A x)_s = sum of the partial sums of shared DoF s, in the fixed order of its
-// batches (red_idx holds their positions in the batch-ordered partial
-// buffer), then the fused step
-template <typename S, typename T, int FK>
-__global__ void reduce_shared_kernel(int64_t n_shared, int nv, const int32_t* __restrict__ red_off,
-                                     const int32_t* __restrict__ red_idx, const T* __restrict__ partial,
-                                     T* __restrict__ dst, FusedStep fs) {
-  const int64_t n = n_shared * nv;
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t sd = i / nv;
-    const int v = static_cast<int>(i - sd * nv);
-    T acc = T(0);
-    for (int j = red_off[sd]; j < red_off[sd + 1]; ++j)
-      acc += partial[static_cast<int64_t>(red_idx[j]) * nv + v];
-    finish_dof<S, T, FK>(fs, sd, nv, v, acc, dst);
-  }
-}
-
-// The same for NV interleaved vectors, one thread per shared DoF: the NV
-// values of a partial sum are one aligned vector load, its index is read once
-// for all of them, and every value is summed in the same order as above
-template <typename S, typename T, int FK, int NV>
-__global__ void reduce_shared_vec_kernel(int64_t n_shared, const int32_t* __restrict__ red_off,
-                                         const int32_t* __restrict__ red_idx, const T* __restrict__ partial,
-                                         T* __restrict__ dst, FusedStep fs) {
-  typedef T VecT __attribute__((ext_vector_type(NV)));
-  for (int64_t sd = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; sd < n_shared;
-       sd += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    VecT acc = T(0);
-    for (int j = red_off[sd]; j < red_off[sd + 1]; ++j)
-      acc += *reinterpret_cast<const VecT*>(partial + static_cast<int64_t>(red_idx[j]) * NV);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) finish_dof<S, T, FK>(fs, sd, NV, v, acc[v], dst);
-  }
-}
-
 // Does the hanging-node interpolation C_e touch node (a, b, c)?  Only if one
 // of the three lines through the node is interpolated: otherwise C_e e_s =
 // e_s for its slot s (the in-place line interpolations mix values along
@@ -1265,12 +395,12 @@ template <int K>
 __global__ void __launch_bounds__((K + 1) * (K + 1))
     diag_mapped_kernel(const int32_t* __restrict__ ent, const uint32_t* __restrict__ mask, int64_t nc,
                        const double* __restrict__ geo, const int32_t* __restrict__ ijk, int n0,
-                       MapTab<double, K + 1> mt, OpTab2<double, K + 1> tab, double* __restrict__ diag,
+                       MapTab<double, K + 1> mt, HangTab<double, K + 1> tab, double* __restrict__ diag,
                        const int32_t* __restrict__ cells) {
   constexpr int N = K + 1, N2 = N * N, N3 = N2 * N;
   __shared__ double B[N3];
   __shared__ double Hg[2 * N2];
-  for (int i = threadIdx.x; i < 2 * N2; i += blockDim.x) Hg[i] = tab.Hg[i];
+  for (int i = threadIdx.x; i < 2 * N2; i += blockDim.x) Hg[i] = tab.v[i];
   __syncthreads();
   const int64_t cell = cells ? cells[blockIdx.x] : blockIdx.x;
   const int ta = threadIdx.x % N, tb = threadIdx.x / N;
@@ -1453,15 +583,6 @@ __global__ void __launch_bounds__((K + 1) * (K + 1))
 
 // ---------------------------------------------------------------------------
 // vector kernels
-constexpr int VEC_THREADS = 256;
-
-inline unsigned grid_for(int64_t n, int per_thread = 1) {
-  int64_t b = (n + static_cast<int64_t>(VEC_THREADS) * per_thread - 1) / (static_cast<int64_t>(VEC_THREADS) * per_thread);
-  if (b < 1) b = 1;
-  if (b > 1 << 20) b = 1 << 20;
-  return static_cast<unsigned>(b);
-}
-
 __global__ void fill_zero_kernel(uint32_t* __restrict__ x, int64_t nwords) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < nwords;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
@@ -1666,124 +787,6 @@ void zero_bytes(void* p, int64_t bytes, hipStream_t s) {
   check_launch();
 }
 
-template <int K, typename S, int FK, int GEO, bool DET>
-void vmult_run(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s) {
-  using T = typename Acc<S>::type;
-  constexpr int N = K + 1;
-  if (c.n_cells == 0) return;
-  static const OpTab2<T, N> tab = make_optab2<T, N>();
-  static const MapTab<T, N> mt = make_maptab<T, N>();
-  if constexpr (GEO == 0) ensure_hg_table<T, N>();
-  const T* geo = nullptr;
-  if constexpr (GEO != 0) geo = static_cast<const T*>(sizeof(T) == 8 ? c.geo64 : c.geo32);
-  // persistent blocks: as many as are resident on the device at once (a
-  // multiple of 8, one share per XCD), at most one per batch
-  static const int64_t resident = [] {
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void*>(&vmult_batch_kernel<K, S, T, FK, GEO, DET>), BATCH_WAVES * 64, 0) !=
-            hipSuccess) {
-      (void)hipGetLastError();
-      return int64_t(0);
-    }
-    return static_cast<int64_t>(cus) * per_cu * BATCH_GRID_FACTOR;
-  }();
-  const int64_t nb = c.n_batches;
-  int64_t blocks = 8 * ((nb * nv + 7) / 8);  // (several vectors: one block per (batch, vector) at most)
-  if (resident >= 8 && blocks > resident / 8 * 8) blocks = resident / 8 * 8;
-  if (blocks < 8 * nv) blocks = 8 * nv;  // every XCD runs all vectors of a batch together
-  constexpr bool atom = (FK & FUSE_ATOMIC) != 0;
-  constexpr bool into_dst = base_kind(FK) == FUSE_NONE;
-  if (atom && c.n_shared > 0) {  // (the shared DoFs are the first n_shared)
-    clear_shared_kernel<T><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(
-        c.n_shared, static_cast<T*>(into_dst ? dst : c.partial));
-    check_launch();
-  }
-  vmult_batch_kernel<K, S, T, FK, GEO, DET><<<static_cast<unsigned>(blocks), BATCH_WAVES * 64, 0, s>>>(
-      c.meta, c.batch_cell, c.batch_sh, c.batch_ex, c.sh_idx, nb, c.n_shared, c.h0, tab,
-      static_cast<const S*>(src), static_cast<T*>(c.partial), static_cast<T*>(dst), nv, f, geo, c.ijk, c.geo_n0,
-      mt);
-  check_launch();
-  if constexpr (atom && !into_dst) {
-    if (c.n_shared > 0) {
-      finish_shared_kernel<S, T, base_kind(FK)><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(
-          c.n_shared, static_cast<const T*>(c.partial), static_cast<T*>(dst), f);
-      check_launch();
-    }
-  }
-  if constexpr (!atom) {
-    if (c.n_shared > 0) {
-      const T* part = static_cast<const T*>(c.partial);  // (256-byte aligned: vector loads of NV values)
-      T* out = static_cast<T*>(dst);
-      const unsigned g = grid_for(c.n_shared);
-      if (nv == 8) {
-        reduce_shared_vec_kernel<S, T, FK, 8><<<g, VEC_THREADS, 0, s>>>(c.n_shared, c.red_off, c.red_idx, part, out, f);
-      } else if (nv == 4) {
-        reduce_shared_vec_kernel<S, T, FK, 4><<<g, VEC_THREADS, 0, s>>>(c.n_shared, c.red_off, c.red_idx, part, out, f);
-      } else if (nv == 2) {
-        reduce_shared_vec_kernel<S, T, FK, 2><<<g, VEC_THREADS, 0, s>>>(c.n_shared, c.red_off, c.red_idx, part, out, f);
-      } else {
-        reduce_shared_kernel<S, T, FK><<<grid_for(c.n_shared * nv), VEC_THREADS, 0, s>>>(
-            c.n_shared, nv, c.red_off, c.red_idx, part, out, f);
-      }
-      check_launch();
-    }
-  }
-}
-
-// One vector: the shared DoFs' sums go out with global atomics, which run
-// alongside the evaluation and replace the partial sums' write and the
-// reduction's gathers.  Interleaved vectors keep the partial sums (their
-// atomics would meet in one line, which measured slower), and so does the
-// deterministic mode (their fixed order).
-template <int K, typename S, int FK, int GEO, bool DET>
-void vmult_kgd(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s) {
-  if constexpr (!DET) {
-    if (nv == 1) {
-      vmult_run<K, S, FK | FUSE_ATOMIC, GEO, false>(c, nv, dst, src, f, s);
-      return;
-    }
-  }
-  vmult_run<K, S, FK, GEO, DET>(c, nv, dst, src, f, s);
-}
-
-template <int K, typename S, int FK, int GEO>
-void vmult_kg(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s) {
-  if (c.deterministic) vmult_kgd<K, S, FK, GEO, true>(c, nv, dst, src, f, s);
-  else vmult_kgd<K, S, FK, GEO, false>(c, nv, dst, src, f, s);
-}
-
-template <int K, typename S, int FK>
-void vmult_k(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s) {
-  if (c.geo64) vmult_kg<K, S, FK, 1>(c, nv, dst, src, f, s);
-  else vmult_kg<K, S, FK, 0>(c, nv, dst, src, f, s);
-}
-
-template <int K, typename S>
-void vmult_kf(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s) {
-  switch (f.kind) {
-    case FUSE_NONE: vmult_k<K, S, FUSE_NONE>(c, nv, dst, src, f, s); break;
-    case FUSE_CHEB: vmult_k<K, S, FUSE_CHEB>(c, nv, dst, src, f, s); break;
-    case FUSE_RESIDUAL: vmult_k<K, S, FUSE_RESIDUAL>(c, nv, dst, src, f, s); break;
-    default: throw Error(MFMG_ERR_INVALID_ARG, "fused step");
-  }
-}
-
-template <typename S>
-void vmult_s(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s) {
-  switch (c.k) {
-    case 1: vmult_kf<1, S>(c, nv, dst, src, f, s); break;
-    case 2: vmult_kf<2, S>(c, nv, dst, src, f, s); break;
-    case 3: vmult_kf<3, S>(c, nv, dst, src, f, s); break;
-    case 4: vmult_kf<4, S>(c, nv, dst, src, f, s); break;
-    case 5: vmult_kf<5, S>(c, nv, dst, src, f, s); break;
-    case 6: vmult_kf<6, S>(c, nv, dst, src, f, s); break;
-    default: throw Error(MFMG_ERR_UNSUPPORTED, "degree");
-  }
-}
-
 // One launch over all cells (cells = NULL: block i is cell i), or in the
 // deterministic mode one launch per colour over that colour's cell list.
 template <typename F>
@@ -1805,7 +808,7 @@ void diag_k(const CellView& c, double* diag, hipStream_t s) {
   if (c.n_cells == 0) return;
   if (c.geo64) {
     static const MapTab<double, N> mt = make_maptab<double, N>();
-    static const OpTab2<double, N> tab2 = make_optab2<double, N>();
+    static const HangTab<double, N> tab2 = make_hangtab<double, N>();
     static const DiagTab<double, N> dt = [] {
       const Tables1D& t = tables(N - 1);
       DiagTab<double, N> r;
@@ -1856,9 +859,9 @@ void rhs_k(const CellView& c, int kind, const double* params, int n_terms, int n
 void launch_vmult_fused(const CellView& c, int dtype, int nv, void* dst, const void* src, const FusedStep& f,
                         hipStream_t s) {
   switch (dtype) {
-    case MFMG_F64: vmult_s<double>(c, nv, dst, src, f, s); break;
-    case MFMG_F32: vmult_s<float>(c, nv, dst, src, f, s); break;
-    case MFMG_BF16: vmult_s<bf16>(c, nv, dst, src, f, s); break;
+    case MFMG_F64: vmult_f64(c, nv, dst, src, f, s); break;
+    case MFMG_F32: vmult_f32(c, nv, dst, src, f, s); break;
+    case MFMG_BF16: vmult_bf16(c, nv, dst, src, f, s); break;
     default: throw Error(MFMG_ERR_UNSUPPORTED, "dtype");
   }
 }
@@ -2080,7 +1083,7 @@ __global__ void coef_apply_kernel(int64_t n, const double* __restrict__ c, uint3
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const uint32_t m = (mask[i] & ~MASK_COEF_BITS) | coef_bits(c[i]);
     mask[i] = m;
-    meta[i].mask = m;
+    meta[i].mask = (meta[i].mask & ~MASK_COEF_BITS) | (m & MASK_COEF_BITS);  // (it has its own orientation bits)
   }
 }
 }  // namespace

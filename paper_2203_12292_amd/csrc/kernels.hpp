@@ -7,12 +7,15 @@
 
 namespace mfmg {
 
-// Per-cell record of the operator (one 64-byte line): local entity starts of
-// the 27 slots in the batch's LDS vector (0xffff: Dirichlet) and the mask.
+// Per-cell record of the operator (one 64-byte line): the mask and the local
+// starts of the cell's 27 entities in the batch's LDS vector (Dirichlet ones
+// start at the zero block behind it).  Axis-aligned cells: one row of ten
+// entries per class of z (0, inner, k), the entity of classes cx and cy at
+// position 3 cy + cx of its row, in the record's own axes (op_axis; the mask
+// too).  Mapped cells: the 27 slots in order.
 struct alignas(64) CellMeta {
-  uint16_t loc[28];
+  uint16_t loc[30];
   uint32_t mask;
-  uint32_t pad;
 };
 static_assert(sizeof(CellMeta) == 64, "CellMeta must be one 64-byte line");
 
@@ -30,6 +33,8 @@ struct CellView {
   // cell batches of the operator (see dofs.hpp)
   int64_t n_batches = 0;
   const CellMeta* meta = nullptr;     // [n_cells]
+  int max_batch_cells = 0, max_batch_dofs = 0;
+  const void* eig = nullptr;          // 1D eigenbasis (eig.hpp), axis-aligned cells
   const int32_t* batch_cell = nullptr;
   const int32_t* batch_sh = nullptr;
   const int32_t* batch_ex = nullptr;
@@ -98,6 +103,9 @@ struct TransferView {
 // "acc" vectors are double for F64 and float otherwise.
 
 // dst_acc = A src (every entry written; no initialisation needed)
+void vmult_f64(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s);
+void vmult_f32(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s);
+void vmult_bf16(const CellView& c, int nv, void* dst, const void* src, const FusedStep& f, hipStream_t s);
 void launch_vmult(const CellView& c, int dtype, int nv, void* dst_acc, const void* src, hipStream_t s);
 // operator application with a fused elementwise step on its output (dst_acc
 // unused unless f.kind is FUSE_NONE)

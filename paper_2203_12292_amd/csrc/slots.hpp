@@ -83,6 +83,13 @@ __host__ __device__ constexpr bool batch_meta_in_lds(int k) { return k >= 5; }
 __host__ __device__ constexpr int batch_max_cells(int k) {
   return batch_meta_in_lds(k) ? 2 * BATCH_WAVES * cells_per_wave(k + 1) : BATCH_MAX_CELLS;
 }
+// Bound on a batch's cells by degree: the operator's block has a lane (up to
+// degree 2) or k+1 lanes for each of them.  (The DoFs bound them first: the
+// largest batches met hold 560 cells at degree 2, 144 at degree 3, 48 at
+// degree 4.)
+__host__ __device__ constexpr int batch_max_cells_hard(int k) {
+  return k <= 2 ? BATCH_MAX_CELLS : k == 3 ? 256 : k == 4 ? 96 : batch_max_cells(k);
+}
 #ifndef MFMG_BATCH_QUANTIZE
 #define MFMG_BATCH_QUANTIZE 1
 #endif
@@ -137,6 +144,19 @@ __host__ __device__ inline uint32_t coef_bits(double c) {
     ++e;
   }
   return static_cast<uint32_t>(e) << 24 | m7 << 9;
+}
+
+// Mask of the operator's records of axis-aligned cells: cells with hanging
+// nodes are reflected and permuted so that their parent's corner is node
+// (0,0,0) and hanging faces are normal to the first axes.  Bits 0-2: the axis
+// runs against the cell's own; 3-8: hanging faces and edges, in the new axes;
+// 16-20: level; 21-23: the permutation (op_axis).
+__host__ __device__ inline int op_level(uint32_t m) { return (m >> 16) & 0x1f; }
+// the cell's own axis that axis d of the record runs along
+__host__ __device__ inline int op_axis(uint32_t m, int d) {
+  const int p = (m >> 21) & 7;  // 012, 021, 102, 120, 201, 210
+  const int a = p >> 1, b = (p & 1) ? (a == 2 ? 1 : 2) : (a == 0 ? 1 : 0);
+  return d == 0 ? a : d == 1 ? b : 3 - a - b;
 }
 
 // Is the line along axis d through local node indices (p, q) of the other two

@@ -8,8 +8,10 @@
 #include <unordered_map>
 
 #include "context.hpp"
+#include "eig.hpp"
 #include "fe1d.hpp"
 #include "net.hpp"
+#include "slots.hpp"
 
 namespace mfmg {
 
@@ -198,6 +200,46 @@ void upload_into(DeviceArray<T>& d, const std::vector<T>& h) { d.upload(h); }
 }  // namespace
 
 namespace {
+// The operator's record of an axis-aligned cell: its entities in the cell's own
+// order, or for a cell with hanging nodes reflected and permuted (slots.hpp).
+// An entity starts at the node that comes first in the record's order.  zb:
+// start of the zero block, for absent entities.
+CellMeta oriented_record(const LevelDofs& H, int64_t c, int zb) {
+  const uint32_t m = H.mask[c];
+  const int km = H.k - 1;
+  int axis[3] = {0, 1, 2};
+  bool flip[3] = {false, false, false};  // by the cell's own axis
+  CellMeta M{};
+  M.mask = (m & (MASK_COEF_BITS | 0x1f0000u));
+  if (mask_hanging(m)) {
+    // hanging faces first, then hanging edges
+    std::stable_sort(axis, axis + 3, [&](int a, int b) {
+      return 2 * mask_face(m, a) + mask_edge(m, a) > 2 * mask_face(m, b) + mask_edge(m, b);
+    });
+    for (int d = 0; d < 3; ++d) {
+      flip[axis[d]] = mask_sub(m, axis[d]) != 0;
+      M.mask |= static_cast<uint32_t>(mask_sub(m, axis[d])) << d | static_cast<uint32_t>(mask_face(m, axis[d])) << (3 + d) |
+                static_cast<uint32_t>(mask_edge(m, axis[d])) << (6 + d);
+    }
+    const int second = axis[1] > axis[2] ? 1 : 0;  // of the two axes left, in descending order
+    M.mask |= static_cast<uint32_t>(2 * axis[0] + second) << 21;
+  }
+  for (int e = 0; e < N_SLOTS; ++e) {
+    const int cls[3] = {e % 3, (e / 3) % 3, e / 9};  // classes along the record's axes: 0, inner, k
+    int own[3];
+    for (int d = 0; d < 3; ++d) own[axis[d]] = flip[axis[d]] ? 2 - cls[d] : cls[d];
+    const uint16_t l = H.loc[node_slot(own[0], own[1], own[2], 2) * H.n_cells + c];
+    int first = l == batch_mcap(H.k) ? zb : l, stride = 1;
+    for (int a = 0; a < 3; ++a)
+      if (own[a] == 1) {
+        if (flip[a] && km > 1) first += (km - 1) * stride;
+        stride *= km;
+      }
+    M.loc[10 * (e / 9) + e % 9] = static_cast<uint16_t>(first);
+  }
+  return M;
+}
+
 // Device data of one level from its host description; `work` allocates the
 // V-cycle work vectors.
 void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work, hipStream_t s) {
@@ -226,14 +268,30 @@ void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work
   L.view.h0 = H.h0;
   L.view.lo = lo;
   {
+    int max_cells = 0, max_dofs = 0;
+    for (int64_t b = 0; b < H.n_batches; ++b) {
+      max_cells = std::max(max_cells, H.batch_cell_off[b + 1] - H.batch_cell_off[b]);
+      max_dofs = std::max(max_dofs, H.batch_sh_off[b + 1] - H.batch_sh_off[b] + H.batch_ex_off[b + 1] -
+                                        H.batch_ex_off[b]);
+    }
+    L.view.max_batch_cells = max_cells;
+    L.view.max_batch_dofs = max_dofs;
     std::vector<CellMeta> meta(H.n_cells);
     for (int64_t c = 0; c < H.n_cells; ++c) {
-      for (int sl = 0; sl < N_SLOTS; ++sl) meta[c].loc[sl] = H.loc[sl * H.n_cells + c];
-      meta[c].loc[27] = 0xffff;
-      meta[c].mask = H.mask[c];
-      meta[c].pad = 0;
+      if (ctx.geo.kind == 0) {
+        meta[c] = oriented_record(H, c, max_dofs);
+        continue;
+      }
+      CellMeta& M = meta[c];
+      M = CellMeta{};
+      M.mask = H.mask[c];
+      for (int e = 0; e < N_SLOTS; ++e) M.loc[e] = H.loc[e * H.n_cells + c];
     }
     L.meta.upload(meta);
+  }
+  if (ctx.geo.kind == 0) {
+    L.eig.upload(eig_table(L.k));
+    L.view.eig = L.eig.ptr;
   }
   L.batch_cell.upload(H.batch_cell_off);
   L.batch_sh.upload(H.batch_sh_off);
