@@ -28,7 +28,7 @@ struct Level {
   DeviceArray<uint32_t> mask;
   DeviceArray<CellMeta> meta;
   DeviceArray<int32_t> batch_cell, batch_sh, batch_ex, sh_idx, red_off, red_idx;
-  DeviceArray<char> partial, eig;
+  DeviceArray<char> partial, acc, eig;
   CellView view;
   DeviceArray<double> diag;
   DeviceArray<char> dinv;  // 1/diag in the level's arithmetic type

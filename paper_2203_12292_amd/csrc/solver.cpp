@@ -300,6 +300,9 @@ void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work
   L.red_idx.upload(H.red_idx);
   L.red_off.upload(H.red_off);
   L.partial.alloc(std::max<size_t>(1, H.sh_idx.size()) * ctx.max_rhs * 8);
+  L.acc.alloc(std::max<size_t>(1, H.n_shared) * 8);
+  launch_fill(0, L.acc.ptr, static_cast<int64_t>(L.acc.bytes()), s);
+  L.view.acc = L.acc.ptr;
   L.view.n_batches = H.n_batches;
   L.view.meta = L.meta.ptr;
   L.view.batch_cell = L.batch_cell.ptr;

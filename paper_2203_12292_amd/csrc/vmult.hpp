@@ -101,8 +101,8 @@ __device__ __forceinline__ void finish_dof(const FusedStep& f, int64_t g, int nv
 // one contiguous range), the cells are evaluated group by group from LDS and
 // their contributions accumulated in LDS, then the exclusive DoFs are stored
 // contiguously and the shared DoFs either added with global atomics
-// (FUSE_ATOMIC route, one vector: into dst, or into the accumulator in the
-// partial buffer when a step is fused; either cleared before) or written as
+// (FUSE_ATOMIC route, one vector: into dst, or into the level's accumulator
+// when a step is fused; either clear before) or written as
 // this batch's partial sums (reduced afterwards).  gridDim.x is a multiple
 // of 8.
 // register budget: the three gradient components and the metric terms of a
@@ -398,9 +398,9 @@ struct HangBits {
 // range), every cell of the batch is gathered into registers at once, worked on,
 // and accumulated in LDS (FP64) in the place of the staged input; exclusive
 // DoFs are stored contiguously and the shared ones either added with global
-// atomics (FUSE_ATOMIC route, one vector: into dst, or into the accumulator in
-// the partial buffer when a step is fused; either cleared before) or written
-// as this batch's partial sums (reduced afterwards).
+// atomics (FUSE_ATOMIC route, one vector: into dst, or into the level's
+// accumulator when a step is fused; either clear before) or written as this
+// batch's partial sums (reduced afterwards).
 //
 // A cell takes n lanes, one per plane (x, y) of its nodes: the x- and y-sweeps
 // run in registers, and one exchange each way between the cell's lanes through
@@ -855,12 +855,17 @@ __global__ void clear_shared_kernel(int64_t n, T* __restrict__ dst) {
 }
 
 // the fused step on the shared DoFs of one vector, from their sums (A x)_s
-// accumulated atomically in acc
+// accumulated atomically in acc, which is left cleared for the next operator
+// application (a clearing launch of its own costs a small level as much as the
+// operator: Q2 solve of 2,808 cells 3.59 -> 3.32 ms without it)
 template <typename S, typename T, int FK>
-__global__ void finish_shared_kernel(int64_t n_shared, const T* __restrict__ acc, T* __restrict__ dst, FusedStep fs) {
+__global__ void finish_shared_kernel(int64_t n_shared, T* __restrict__ acc, T* __restrict__ dst, FusedStep fs) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n_shared;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    finish_dof<S, T, FK>(fs, i, 1, 0, acc[i], dst);
+       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    const T t = acc[i];
+    acc[i] = T(0);
+    finish_dof<S, T, FK>(fs, i, 1, 0, t, dst);
+  }
 }
 
 // (A x)_s = sum of the partial sums of shared DoF s, in the fixed order of its
@@ -907,9 +912,12 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
   if (c.n_cells == 0) return;
   constexpr bool atom = (FK & FUSE_ATOMIC) != 0;
   constexpr bool into_dst = base_kind(FK) == FUSE_NONE;
-  if (atom && c.n_shared > 0) {  // (the shared DoFs are the first n_shared)
-    clear_shared_kernel<T><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(
-        c.n_shared, static_cast<T*>(into_dst ? dst : c.partial));
+  // shared sums: added atomically into dst, cleared first (the shared DoFs are
+  // the first n_shared), or for a fused step into the level's accumulator,
+  // which every finish leaves cleared; else partial sums
+  T* sums = static_cast<T*>(atom && !into_dst ? c.acc : c.partial);
+  if (atom && into_dst && c.n_shared > 0) {
+    clear_shared_kernel<T><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(c.n_shared, static_cast<T*>(dst));
     check_launch();
   }
   const int64_t nb = c.n_batches;
@@ -936,7 +944,7 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
     if (blocks < 8 * nv) blocks = 8 * nv;  // every XCD runs all vectors of a batch together
     vmult_mapped_kernel<K, S, T, FK, DET><<<static_cast<unsigned>(blocks), BATCH_WAVES * 64, 0, s>>>(
         c.meta, c.batch_cell, c.batch_sh, c.batch_ex, c.sh_idx, nb, c.n_shared, tab, static_cast<const S*>(src),
-        static_cast<T*>(c.partial), static_cast<T*>(dst), nv, f, geo, c.ijk, c.geo_n0, mt);
+        sums, static_cast<T*>(dst), nv, f, geo, c.ijk, c.geo_n0, mt);
   } else {
     using Y = CellLayout<K>;
     using C = CellReal;
@@ -954,13 +962,13 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
     const int64_t blocks = 8 * run * ((nb + 8 * run - 1) / (8 * run)) * nv;
     vmult_batch_kernel<K, S, T, FK, DET><<<static_cast<unsigned>(blocks), 64 * waves, lds, s>>>(
         c.meta, c.batch_cell, c.batch_sh, c.batch_ex, c.sh_idx, static_cast<int>(nb), static_cast<int>(run), c.n_shared, c.max_batch_dofs, c.h0, tab,
-        static_cast<const S*>(src), static_cast<T*>(c.partial), static_cast<T*>(dst), nv, f);
+        static_cast<const S*>(src), sums, static_cast<T*>(dst), nv, f);
   }
   check_launch();
   if constexpr (atom && !into_dst) {
     if (c.n_shared > 0) {
       finish_shared_kernel<S, T, base_kind(FK)><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(
-          c.n_shared, static_cast<const T*>(c.partial), static_cast<T*>(dst), f);
+          c.n_shared, sums, static_cast<T*>(dst), f);
       check_launch();
     }
   }
