@@ -165,13 +165,18 @@ void launch_dense_matvec(int dtype, int64_t n0, int nv, const void* Ainv, const 
                          void* acc_tmp, hipStream_t s);
 
 // ---- FP64 CG helpers --------------------------------------------------------
-// partial[blk*nv+v] = sum_i a[i*nv+v]*b[i*nv+v]; result[v] via second stage.
+// result[v] = sum_i a[i*nv+v]*b[i*nv+v].  partial: dot_partials_needed()
+// doubles of work space (dot products that share one must be ordered on one
+// stream)
+int dot_partials_needed();
 void launch_dot(int64_t n_dofs, int nv, const double* a, const double* b, double* partial, double* result,
                 hipStream_t s);
-int dot_partials_needed();
-// x += alpha[v] p; r -= alpha[v] q   with alpha = num[v]/den[v]
+// result_b = a . b and result_c = a . c
+void launch_dot2(int64_t n_dofs, int nv, const double* a, const double* b, const double* c, double* partial,
+                 double* result_b, double* result_c, hipStream_t s);
+// x += alpha[v] p; r -= alpha[v] q   with alpha = num[v]/den[v]; rr[v] = r . r
 void launch_cg_update_xr(int64_t n_dofs, int nv, const double* num, const double* den, const double* p,
-                         const double* q, double* x, double* r, hipStream_t s);
+                         const double* q, double* x, double* r, double* partial, double* rr, hipStream_t s);
 // p = z + beta[v] p  with beta = (num[v] - sub[v]) / den[v] (sub may be null)
 void launch_cg_update_p(int64_t n_dofs, int nv, const double* num, const double* sub, const double* den,
                         const double* z, double* p, hipStream_t s);

@@ -166,7 +166,7 @@ void estimate_eigenvalues(Context& ctx, Level& L, int iters, double safety, doub
     sync(s);
     if (!(pap > 0.0) || !(rz > 0.0)) break;
     // r -= alpha q (x unused)
-    launch_cg_update_xr(n, 1, sc.ptr + 0, sc.ptr + 1, p.ptr, q.ptr, x.ptr, r.ptr, s);
+    launch_cg_update_xr(n, 1, sc.ptr + 0, sc.ptr + 1, p.ptr, q.ptr, x.ptr, r.ptr, part.ptr, sc.ptr + 3, s);
     precond(z.ptr, r.ptr);
     launch_dot(n, 1, r.ptr, z.ptr, part.ptr, sc.ptr + 2, s);  // rz_new
     double rzn;
@@ -563,7 +563,7 @@ void setup_context(Context& ctx, const mfmg_mesh_s& mesh, const mfmg_level_desc&
   ctx.cg_q.alloc(nf);
   ctx.cg_z.alloc(nf);
   ctx.cg_zold.alloc(nf);
-  ctx.cg_partial.alloc(static_cast<size_t>(dot_partials_needed()) * 8);
+  ctx.cg_partial.alloc(dot_partials_needed());
   ctx.cg_scalar.alloc(8 * 8);
   ctx.host_scalar.assign(8 * 8, 0.0);
   ctx.rhs_params.alloc(static_cast<size_t>(5) * 8 * ctx.max_rhs);  // 8 Gaussians per vector
@@ -898,12 +898,12 @@ int pcg(Context& ctx, int nv, double* x, const double* b, double rtol, int max_i
     for (it = 1; it <= max_it; ++it) {
       launch_vmult(F.view, MFMG_F64, nv, ctx.cg_q.ptr, ctx.cg_p.ptr, s);
       launch_dot(n, nv, ctx.cg_p.ptr, ctx.cg_q.ptr, ctx.cg_partial.ptr, pq, s);
-      launch_cg_update_xr(n, nv, rz, pq, ctx.cg_p.ptr, ctx.cg_q.ptr, x, ctx.cg_r.ptr, s);
-      launch_dot(n, nv, ctx.cg_r.ptr, ctx.cg_r.ptr, ctx.cg_partial.ptr, rr, s);
-      std::vector<double> hpq(nv);
-      MFMG_HIP(hipMemcpyAsync(hr.data(), rr, nv * 8, hipMemcpyDeviceToHost, s));
-      MFMG_HIP(hipMemcpyAsync(hpq.data(), pq, nv * 8, hipMemcpyDeviceToHost, s));
+      launch_cg_update_xr(n, nv, rz, pq, ctx.cg_p.ptr, ctx.cg_q.ptr, x, ctx.cg_r.ptr, ctx.cg_partial.ptr, rr, s);
+      // (pq and rr are neighbours: one copy)
+      MFMG_HIP(hipMemcpyAsync(ctx.host_scalar.data(), pq, 16 * 8, hipMemcpyDeviceToHost, s));
       sync(s);
+      const double* hpq = ctx.host_scalar.data();
+      for (int v = 0; v < nv; ++v) hr[v] = ctx.host_scalar[8 + v];
       worst = 0.0;
       bool breakdown = false;
       for (int v = 0; v < nv; ++v) {
@@ -917,10 +917,12 @@ int pcg(Context& ctx, int nv, double* x, const double* b, double rtol, int max_i
       if (breakdown) { status = MFMG_ERR_BREAKDOWN; break; }
       if (flexible) std::swap(ctx.cg_z.ptr, ctx.cg_zold.ptr);
       solver_vcycle(ctx, nv, ctx.cg_z.ptr, ctx.cg_r.ptr, s);
-      launch_dot(n, nv, ctx.cg_r.ptr, ctx.cg_z.ptr, ctx.cg_partial.ptr, rzn, s);
-      if (flexible) launch_dot(n, nv, ctx.cg_r.ptr, ctx.cg_zold.ptr, ctx.cg_partial.ptr, rzo, s);
+      if (flexible)
+        launch_dot2(n, nv, ctx.cg_r.ptr, ctx.cg_z.ptr, ctx.cg_zold.ptr, ctx.cg_partial.ptr, rzn, rzo, s);
+      else
+        launch_dot(n, nv, ctx.cg_r.ptr, ctx.cg_z.ptr, ctx.cg_partial.ptr, rzn, s);
       launch_cg_update_p(n, nv, rzn, flexible ? rzo : nullptr, rz, ctx.cg_z.ptr, ctx.cg_p.ptr, s);
-      MFMG_HIP(hipMemcpyAsync(rz, rzn, nv * 8, hipMemcpyDeviceToDevice, s));
+      std::swap(rz, rzn);
     }
     if (it > max_it) it = max_it;
   }
