@@ -114,7 +114,11 @@ struct TrLds {
   static constexpr int N = Y + (LINES ? NC * NF * NF : 0);
 };
 
-// What bounds it: HBM traffic.  A wavefront works on its own groups without
+// What bounds it: HBM traffic (Q3 -> Q6, 8 FP32 vectors: 4.2 GB in 1.00 ms;
+// the restriction's 2.3 GB in 1.11 ms, beside 1.4e8 atomic adds; 4.3 and 4.2 ms
+// with one 256-thread block per group and its nodes looked up one by one).  On
+// one vector latency (Q4 prolongation onto 17M FP64 DoFs 110 us, 326 before).
+// A wavefront works on its own groups without
 // block barriers.  All index data of a group is one contiguous record (the
 // first DoF of each lattice entity, -1 where another group owns it or it is
 // constrained).  A lane owns one x index of the fine lattice and one vector,
@@ -126,7 +130,8 @@ struct TrLds {
 // LINES (one vector): the lanes go over the z-lines of the fine lattice
 // instead, x fastest, with the y-sweep through LDS.  A load then covers the
 // runs of whole faces and interiors ((k-1)^2 adjacent values) where the
-// planes' load covers one row of each of several groups, k-1 values apiece.
+// planes' load covers one row of each of several groups, k-1 values apiece
+// (the same prolongation 110 us by lines, 156 us by planes at its best).
 template <int KF, int KC, int NF, typename S, typename T, bool PROLONG, bool LINES>
 __global__ void __launch_bounds__(64 * TR_WAVES)
     transfer_kernel(const int32_t* __restrict__ fdesc, const int32_t* __restrict__ cdesc, int64_t n_groups,
