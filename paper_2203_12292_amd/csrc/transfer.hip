@@ -114,8 +114,8 @@ struct TrLds {
   static constexpr int N = Y + (LINES ? NC * NF * NF : 0);
 };
 
-// What bounds it: HBM traffic (Q3 -> Q6, 8 FP32 vectors: 4.2 GB in 1.00 ms;
-// the restriction's 2.3 GB in 1.11 ms, beside 1.4e8 atomic adds; 4.3 and 4.2 ms
+// What bounds it: HBM traffic (Q3 -> Q6, 8 FP32 vectors: 4.5 GB in 1.00 ms;
+// the restriction's 2.8 GB in 1.11 ms, beside 1.4e8 atomic adds; 4.3 and 4.2 ms
 // with one 256-thread block per group and its nodes looked up one by one).  On
 // one vector latency (Q4 prolongation onto 17M FP64 DoFs 110 us, 326 before).
 // A wavefront works on its own groups without

@@ -413,7 +413,7 @@ struct HangBits {
 // What bounds it (Q4, 67.8M FP64 DoFs, 0.42 ms against 0.78 ms by lines): its
 // HBM traffic, 1.6 GB (1.1 GB of vectors, the atomic adds and the index list of
 // the shared DoFs), takes 0.35 ms at the 4.7 TB/s of a plain copy.  Q6 on 8
-// FP32 vectors (3.4 ms against 6.15 ms): VALU about 60 % busy, two wavefronts
+// FP32 vectors (3.4 ms against 6.15 ms): VALU 58 % busy, two wavefronts
 // per SIMD.
 //
 // Cells with hanging nodes come with their axes reflected and permuted (the
