@@ -411,8 +411,9 @@ struct HangBits {
 // addresses per plane instead of two per line.
 //
 // What bounds it (Q4, 67.8M FP64 DoFs, 0.42 ms against 0.78 ms by lines): its
-// HBM traffic, 1.6 GB (1.1 GB of vectors, the atomic adds and the index list of
-// the shared DoFs), takes 0.35 ms at the 4.7 TB/s of a plain copy.  Q6 on 8
+// HBM traffic, 2.05 GB with the clearing (vectors, repeated reads of the shared
+// DoFs, their index list and atomic adds), takes 0.44 ms at the 4.7 TB/s of a
+// plain copy; runs of 16 to 512 batches an XCD instead of 4 change nothing.  Q6 on 8
 // FP32 vectors (3.4 ms against 6.15 ms): VALU 58 % busy, two wavefronts
 // per SIMD.
 //
