@@ -295,11 +295,15 @@ int mfmg_diagonal(mfmg_ctx ctx, int level, int dtype, void* diag, void* stream);
 /* [async] Chebyshev smoothing of degree cheb_degree around point Jacobi
  * (Section 3.3) of A^(l) x = b; x_is_zero: start from x = 0 (skips one
  * operator evaluation).  lambda: NULL for the set-up interval, else
- * {lambda_min, lambda_max}.  Uses the level's internal work vectors. */
+ * {lambda_min, lambda_max}.  Uses the level's internal work vectors: calls
+ * of mfmg_smooth, mfmg_residual and the cycles and solvers built on them that
+ * touch one level must be ordered (one stream, or waits between streams);
+ * where they overlap in time their results are wrong. */
 int mfmg_smooth(mfmg_ctx ctx, int level, int dtype, int n_vec, void* x, const void* b,
                 int x_is_zero, const double* lambda, void* stream);
 
-/* [async] r = b - A^(l) x (Algorithm 2, residual step). */
+/* [async] r = b - A^(l) x (Algorithm 2, residual step).  Uses the level's
+ * internal work vectors, see mfmg_smooth. */
 int mfmg_residual(mfmg_ctx ctx, int level, int dtype, int n_vec, void* r, const void* b,
                   const void* x, void* stream);
 

@@ -29,6 +29,7 @@ struct Level {
   DeviceArray<CellMeta> meta;
   DeviceArray<int32_t> batch_cell, batch_sh, batch_ex, sh_idx, red_off, red_idx;
   DeviceArray<char> partial, acc, eig;
+  std::unique_ptr<bool> acc_unclean = std::make_unique<bool>(false);  // (the view points at it)
   CellView view;
   DeviceArray<double> diag;
   DeviceArray<char> dinv;  // 1/diag in the level's arithmetic type

@@ -42,7 +42,8 @@ struct CellView {
   const int32_t* red_idx = nullptr;
   const int32_t* red_off = nullptr;
   void* partial = nullptr;            // scratch: partial sums, (sh_idx size) x max_rhs x 8 bytes
-  void* acc = nullptr;                // n_shared x 8 bytes, zero between operator applications
+  void* acc = nullptr;                // n_shared x 8 bytes, zero between operator applications ...
+  bool* acc_unclean = nullptr;        // ... unless this says that one broke off
   // mapped cells (geometry.hpp): coarse-cell map coefficients in FP64 and
   // FP32 ([n0^3][24]), NULL for axis-aligned cubes; n0 coarse cells per axis
   const void* geo64 = nullptr;

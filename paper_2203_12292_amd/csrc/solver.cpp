@@ -303,6 +303,7 @@ void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work
   L.acc.alloc(std::max<size_t>(1, H.n_shared) * 8);
   launch_fill(0, L.acc.ptr, static_cast<int64_t>(L.acc.bytes()), s);
   L.view.acc = L.acc.ptr;
+  L.view.acc_unclean = L.acc_unclean.get();
   L.view.n_batches = H.n_batches;
   L.view.meta = L.meta.ptr;
   L.view.batch_cell = L.batch_cell.ptr;

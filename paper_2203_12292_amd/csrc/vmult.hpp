@@ -923,10 +923,15 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
   // the first n_shared), or for a fused step into the level's accumulator,
   // which every finish leaves cleared; else partial sums
   T* sums = static_cast<T*>(atom && !into_dst ? c.acc : c.partial);
-  if (atom && into_dst && c.n_shared > 0) {
-    clear_shared_kernel<T><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(c.n_shared, static_cast<T*>(dst));
+  // a call that throws between the batches and the finish (check_launch also
+  // reports errors that the caller's own HIP calls left behind) leaves the
+  // accumulator marked; the next fused step clears it first
+  const bool unclean = atom && !into_dst && *c.acc_unclean;
+  if (((atom && into_dst) || unclean) && c.n_shared > 0) {
+    clear_shared_kernel<T><<<grid_for(c.n_shared), VEC_THREADS, 0, s>>>(c.n_shared, into_dst ? static_cast<T*>(dst) : sums);
     check_launch();
   }
+  if constexpr (atom && !into_dst) *c.acc_unclean = true;
   const int64_t nb = c.n_batches;
   if constexpr (GEO != 0) {
     static const HangTab<T, N> tab = make_hangtab<T, N>();
@@ -978,6 +983,8 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
           c.n_shared, sums, static_cast<T*>(dst), f);
       check_launch();
     }
+    // (a clearing that was only captured has not run yet: it stays marked)
+    *c.acc_unclean = unclean && capturing(s);
   }
   if constexpr (!atom) {
     if (c.n_shared > 0) {
