@@ -127,7 +127,7 @@ struct TrLds {
 // are loaded while one is worked on; the vector index is the fastest one of
 // the lanes (adjacent lanes touch adjacent memory).
 //
-// LINES (one vector): the lanes go over the z-lines of the fine lattice
+// LINES (one vector per wavefront): the lanes go over the z-lines of the fine lattice
 // instead, x fastest, with the y-sweep through LDS.  A load then covers the
 // runs of whole faces and interiors ((k-1)^2 adjacent values) where the
 // planes' load covers one row of each of several groups, k-1 values apiece
@@ -148,7 +148,10 @@ __global__ void __launch_bounds__(64 * TR_WAVES)
   const int64_t blk = static_cast<int64_t>(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (blk >= n_blocks) return;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-  const int64_t g0 = (blk * TR_WAVES + wave) * groups;
+  // (lines: the vectors of a group are neighbouring wavefronts)
+  const int64_t unit = blk * TR_WAVES + wave;
+  const int only = LINES ? static_cast<int>(unit % nv) : 0;
+  const int64_t g0 = (LINES ? unit / nv : unit) * groups;
   if (g0 >= n_groups) return;  // (no block barriers below)
   const int ng = n_groups - g0 < groups ? static_cast<int>(n_groups - g0) : groups;
   const WaveSync sync{};
@@ -182,10 +185,12 @@ __global__ void __launch_bounds__(64 * TR_WAVES)
   const LatticeRows<KF, NF> rows(pi);
   const int32_t* ef = Ef + pg * FS;
 
-  for (int v0 = 0; v0 < nv; v0 += vb) {
+  for (int v0 = only; v0 < (LINES ? only + 1 : nv); v0 += vb) {
     const int nb = nv - v0 < vb ? nv - v0 : vb;
     const bool mine = pg < ng && pv < nb;
-    auto fine_at = [&](int32_t e) { return static_cast<uint64_t>(static_cast<uint32_t>(e)) * nv + (v0 + pv); };
+    auto fine_at = [&](int32_t e) {
+      return static_cast<uint64_t>(static_cast<uint32_t>(e)) * nv + (LINES ? v0 : v0 + pv);
+    };
     auto load_row = [&](const S* p, int J, T (&w)[NF]) {
       if (mine)
         rows.row(J, ef, [&](int l, int32_t e) { w[l] = e < 0 ? T(0) : load_as<T>(p[fine_at(e)]); });
@@ -197,7 +202,7 @@ __global__ void __launch_bounds__(64 * TR_WAVES)
       if (t >= ng * NF * NF) return;
       const int g = t / (NF * NF), r0 = t - g * NF * NF;
       LatticeRows<KF, NF>(r0 % NF).row(r0 / NF, Ef + g * FS,
-                                       [&](int l, int32_t e) { w[l] = e < 0 ? T(0) : load_as<T>(p[e]); });
+                                       [&](int l, int32_t e) { w[l] = e < 0 ? T(0) : load_as<T>(p[fine_at(e)]); });
     };
     if constexpr (LINES) load_line(PROLONG ? dst : src, lane, next);
     else load_row(PROLONG ? dst : src, 0, next);
@@ -284,7 +289,7 @@ __global__ void __launch_bounds__(64 * TR_WAVES)
             sweep<NC, NF, T, false>(tab.P, u, w);
           }
           LatticeRows<KF, NF>(i).row(j, Ef + g * FS, [&](int l, int32_t e) {
-            if (e >= 0) dst[e] = store_as<S>(old[l] + w[l]);
+            if (e >= 0) dst[fine_at(e)] = store_as<S>(old[l] + w[l]);
           });
         }
       } else {
@@ -448,9 +453,11 @@ TrTab<T, NF, NC> make_trtab(int kf, int kc) {
 }
 
 // Vectors at a time and groups per wavefront.  Planes: NF x 2^lv lanes work on
-// a group, and as many groups as fit fill the wavefront; of the splits whose
-// lanes are at least 80 % as well used as the best one's, the one with the most
-// vectors at a time (wider runs of adjacent memory).  Lines: the fewest groups
+// a group, and as many groups as fit fill the wavefront; 2^lv is the smallest
+// that takes all vectors in one pass, or the largest that fits (a pass more
+// costs more than idle lanes: 3 FP32 vectors, Q3, 270,000 cells, prolongation
+// 237 us in three full passes, 60 us in one with a quarter of the lanes idle;
+// 8 vectors, Q4, 37,000 cells 153 us in four, 86 us in two).  Lines: the fewest groups
 // whose NF^2 lines use 75 % of the lanes of their rounds, within LDS for 14
 // wavefronts per CU (Q4, 30,000 refinement groups: FP32 88 us with one group
 // of 2.5 KB per wavefront, 104 us with three).  Levels with fewer groups than would give every SIMD
@@ -471,18 +478,8 @@ TrShape transfer_shape(int nv, int64_t n_groups, int bytes) {
       }
     }
   } else {
-    double used[4] = {0, 0, 0, 0}, best = 0.0;
-    int g[4] = {1, 1, 1, 1};
-    for (int lv = 0; lv < 4; ++lv) {
-      const int lanes = NF << lv, vb = 1 << lv;
-      if (lanes > 64 || (lv > 0 && vb >= 2 * nv)) continue;
-      g[lv] = 64 / lanes;
-      used[lv] = g[lv] * lanes / 64.0 * nv / static_cast<double>((nv + vb - 1) / vb * vb);
-      best = std::max(best, used[lv]);
-    }
-    s.lv = 3;
-    while (s.lv > 0 && used[s.lv] < 0.8 * best) --s.lv;
-    s.groups = g[s.lv];
+    while ((1 << s.lv) < nv && (NF << (s.lv + 1)) <= 64) ++s.lv;
+    s.groups = 64 / (NF << s.lv);
   }
   s.groups = static_cast<int>(std::min<int64_t>(s.groups, spread));
   return s;
@@ -495,8 +492,9 @@ void transfer_run(const int32_t* fdesc, const int32_t* cdesc, int64_t n, int nv,
   if (n == 0) return;
   static const TrTab<T, NF, KC + 1> tab = make_trtab<T, NF, KC + 1>(KF, KC);
   const TrShape sh = transfer_shape<NF, KC + 1, LINES>(nv, n, sizeof(T));
+  const int64_t units = (n + sh.groups - 1) / sh.groups * (LINES ? nv : 1);  // wavefronts
   const int64_t per_block = static_cast<int64_t>(sh.groups) * TR_WAVES;
-  const int64_t blocks = (n + per_block - 1) / per_block, grid = (blocks + 7) / 8 * 8;
+  const int64_t blocks = (units + TR_WAVES - 1) / TR_WAVES, grid = (blocks + 7) / 8 * 8;
   constexpr int ints = transfer_record(LatticeRows<KF, NF>::NCLS) + transfer_record(3);
   const size_t lds = per_block * (ints * 4 + (TrLds<NF, KC + 1, LINES>::N << sh.lv) * sizeof(T));
   transfer_kernel<KF, KC, NF, S, T, PROLONG, LINES><<<static_cast<unsigned>(grid), 64 * TR_WAVES, lds, s>>>(
@@ -504,10 +502,22 @@ void transfer_run(const int32_t* fdesc, const int32_t* cdesc, int64_t n, int nv,
   check_launch();
 }
 
+// Lines for one vector, and for several on levels with few groups, where a
+// plane's chain of NF rows per lane takes longer than all the rest (64 cells,
+// FP64, 3 vectors, Q6: restriction 93 us by planes, 37 us by lines; Q4 26 and
+// 17 us; prolongation 61 and 27 us, 27 and 16 us).  With more groups the
+// lines' wavefronts, one vector each, touch every line of memory (and the
+// restriction's atomics every line of the coarse vector) n_vec times (8 FP32
+// vectors, Q4, 37,000 cells: restriction 313 us against 79 us).  The two
+// meet at 6,000 (FP64) and 8,000 (FP32) groups x vectors for the prolongation;
+// for the restriction at 5 NF^3, at most 11,000 and 6,000: measured at every
+// degree, 2 to 8 vectors, 64 to 270,000 cells.
 template <int KF, int KC, int NF, typename S, bool PROLONG>
 void transfer_split(const int32_t* fdesc, const int32_t* cdesc, int64_t n, int nv, void* dst, const void* src,
                     bool plain, hipStream_t s) {
-  if (nv == 1) transfer_run<KF, KC, NF, S, PROLONG, true>(fdesc, cdesc, n, nv, dst, src, plain, s);
+  constexpr bool wide = sizeof(typename Acc<S>::type) == 8;
+  constexpr int64_t most = PROLONG ? (wide ? 6000 : 8000) : std::min(5 * NF * NF * NF, wide ? 11000 : 6000);
+  if (nv == 1 || n * nv <= most) transfer_run<KF, KC, NF, S, PROLONG, true>(fdesc, cdesc, n, nv, dst, src, plain, s);
   else transfer_run<KF, KC, NF, S, PROLONG, false>(fdesc, cdesc, n, nv, dst, src, plain, s);
 }
 
