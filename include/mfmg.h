@@ -182,10 +182,11 @@ typedef struct {
   double geom_params[8];
   int deterministic;     /* 1: repeated calls give bitwise identical results
                             (for debugging; slower).  The operator adds its
-                            cells' contributions to a batch in cell order,
-                            one cell at a time, and sums the DoFs shared
-                            between batches from per-batch partial sums in
-                            a fixed order; the restriction, the diagonal
+                            cells' contributions to a batch in groups of
+                            cells that share no DoF (mapped cells: one cell
+                            at a time) and sums the DoFs shared between
+                            batches from per-batch partial sums in a fixed
+                            order; the restriction, the diagonal
                             and the load vector run colour by colour (no
                             two cells or transfer groups of a colour share
                             an entity) with plain adds instead of atomics.

@@ -12,11 +12,14 @@ namespace mfmg {
 // start at the zero block behind it).  Axis-aligned cells: one row of ten
 // entries per class of z (0, inner, k), the entity of classes cx and cy at
 // position 3 cy + cx of its row, in the record's own axes (op_axis; the mask
-// too).  Mapped cells: the 27 slots in order.
+// too); in the deterministic mode the spare entries of the rows hold the
+// cell's phase (cells of a batch with the same one share no entity) and the
+// number of phases of its batch.  Mapped cells: the 27 slots in order.
 struct alignas(64) CellMeta {
   uint16_t loc[30];
   uint32_t mask;
 };
+constexpr int META_PHASE = 29, META_PHASES = 19;  // (spare entries of rows 2 and 1)
 static_assert(sizeof(CellMeta) == 64, "CellMeta must be one 64-byte line");
 
 // Per-level device view of the cell data.
@@ -49,9 +52,10 @@ struct CellView {
   const void* geo64 = nullptr;
   const void* geo32 = nullptr;
   int geo_n0 = 0;
-  // deterministic mode: the operator adds its cells' contributions in cell
-  // order; the diagonal and the load vector run colour by colour (no two
-  // cells of a colour share an entity, plain adds).  color_cells (device)
+  // deterministic mode: the operator adds a batch's cells phase by phase
+  // (mapped cells: in cell order); the diagonal and the
+  // load vector run colour by colour (no two cells of a colour share an
+  // entity, plain adds).  color_cells (device)
   // lists the cells colour by colour, color_off (host, n_colors + 1) the
   // colour ranges.
   bool deterministic = false;

@@ -240,6 +240,37 @@ CellMeta oriented_record(const LevelDofs& H, int64_t c, int zb) {
   return M;
 }
 
+// The phases of the deterministic operator (kernels.hpp), per batch: a cell
+// takes the lowest one that none of its entities has had from a cell before it
+// (a batch has 6 to 34, the colours of a whole level up to three times as many).
+void set_phases(const LevelDofs& H, std::vector<CellMeta>& meta) {
+  std::vector<int32_t> seen(H.n_entities, -1);  // last batch with the entity
+  std::vector<uint64_t> used(H.n_entities, 0);  // its phases there
+  for (int64_t b = 0; b < H.n_batches; ++b) {
+    int phases = 0;
+    for (int64_t c = H.batch_cell_off[b]; c < H.batch_cell_off[b + 1]; ++c) {
+      int32_t ids[26];
+      int n = 0;
+      uint64_t taken = 0;
+      for (int s = 0; s < 26; ++s) {
+        const int32_t id = H.ent_id[s * H.n_cells + c];
+        if (id < 0 || H.ent_size[id] == 0) continue;
+        ids[n++] = id;
+        if (seen[id] != b) used[id] = 0;
+        seen[id] = static_cast<int32_t>(b);
+        taken |= used[id];
+      }
+      MFMG_REQUIRE(taken != ~uint64_t(0), MFMG_ERR_UNSUPPORTED, "deterministic mode: more than 64 phases");
+      const int phase = __builtin_ctzll(~taken);
+      for (int i = 0; i < n; ++i) used[ids[i]] |= uint64_t(1) << phase;
+      meta[c].loc[META_PHASE] = static_cast<uint16_t>(phase);
+      phases = std::max(phases, phase + 1);
+    }
+    for (int64_t c = H.batch_cell_off[b]; c < H.batch_cell_off[b + 1]; ++c)
+      meta[c].loc[META_PHASES] = static_cast<uint16_t>(phases);
+  }
+}
+
 // Device data of one level from its host description; `work` allocates the
 // V-cycle work vectors.
 void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work, hipStream_t s) {
@@ -287,6 +318,16 @@ void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work
       M.mask = H.mask[c];
       for (int e = 0; e < N_SLOTS; ++e) M.loc[e] = H.loc[e * H.n_cells + c];
     }
+    if (ctx.desc.deterministic) {
+      std::vector<int32_t> cells;
+      colour_cells(H, cells, L.color_off);
+      if (ctx.geo.kind == 0) set_phases(H, meta);
+      L.color_cells.upload(cells);
+      L.view.deterministic = true;
+      L.view.color_cells = L.color_cells.ptr;
+      L.view.color_off = L.color_off.data();
+      L.view.n_colors = static_cast<int>(L.color_off.size()) - 1;
+    }
     L.meta.upload(meta);
   }
   if (ctx.geo.kind == 0) {
@@ -328,15 +369,6 @@ void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work
     L.tmp_cast.alloc(nrhs * 8);
   }
   L.t.alloc(nrhs * 8);
-  if (ctx.desc.deterministic) {
-    std::vector<int32_t> cells;
-    colour_cells(H, cells, L.color_off);
-    L.color_cells.upload(cells);
-    L.view.deterministic = true;
-    L.view.color_cells = L.color_cells.ptr;
-    L.view.color_off = L.color_off.data();
-    L.view.n_colors = static_cast<int>(L.color_off.size()) - 1;
-  }
   L.diag.alloc(L.n_dofs);
   L.dinv.alloc(L.n_dofs * 8 * 2);  // double copy, then float copy
   launch_diagonal(L.view, L.diag.ptr, s);

@@ -441,6 +441,7 @@ struct CellLayout {
   // usual batches lets run (Q4 FP64: 4 0.446 ms, 5 0.422 ms; a Q3 smoothing
   // step of 8 FP32 vectors: 4 3.16 ms, 8 2.94 ms)
   static constexpr int WAVES_PER_EU = K <= 2 ? 4 : K == 3 ? 8 : K == 4 ? 5 : 2;
+  static constexpr int WAVES_PER_EU_DET = K <= 4 ? 4 : 2;  // (no spills)
 };
 
 // An opaque copy of the tables' address: their scalar loads stay in the phase
@@ -454,7 +455,7 @@ __device__ __forceinline__ const __attribute__((address_space(4))) P* here(const
 }
 
 template <int K, typename S, typename T, int FK, bool DET>
-__global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(CellLayout<K>::WAVES_PER_EU)))
+__global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(DET ? CellLayout<K>::WAVES_PER_EU_DET : CellLayout<K>::WAVES_PER_EU)))
     vmult_batch_kernel(const CellMeta* __restrict__ meta, const int32_t* __restrict__ bcell,
                       const int32_t* __restrict__ bsh, const int32_t* __restrict__ bex,
                       const int32_t* __restrict__ sh_idx, int nb, int run, int64_t n_shared, int zb, double h0,
@@ -786,6 +787,30 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
   for (int i = tid; i < (m + 1) / 2; i += bt) reinterpret_cast<double2*>(out_)[i] = double2{0.0, 0.0};
   __syncthreads();
   auto scatter_with = [&](auto gen) {
+    if constexpr (DET) {
+      // plain adds of one phase's cells, which share no DoF; the loads of two
+      // rows of nodes (or of a plane of a whole cell) go out together, absent
+      // entities add to the entry behind the batch's DoFs instead of branching
+#pragma unroll
+      for (int i = 0; i < (PLANE ? 9 : 1); ++i) asm volatile("" : "+v"(base[i]));  // (addresses made in each phase)
+#pragma unroll
+      for (int z = 0; z < NZ; ++z) {
+        constexpr int ROWS = PLANE ? 2 : N;
+#pragma unroll
+        for (int y0 = 0; y0 < N; y0 += ROWS) {
+          const int n = (N - y0 < ROWS ? N - y0 : ROWS) * N;
+          int at[ROWS * N];
+          double old[ROWS * N];
+#pragma unroll
+          for (int i = 0; i < n; ++i) at[i] = min(pos(gen, z, y0 + i / N, i % N), zb);
+#pragma unroll
+          for (int i = 0; i < n; ++i) old[i] = out_[at[i]];
+#pragma unroll
+          for (int i = 0; i < n; ++i) out_[at[i]] = old[i] + static_cast<double>(u[z][y0 + i / N][i % N]);
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int e = 0; e < NB; ++e) {
       if (start(e) >= zb) continue;
@@ -796,9 +821,7 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
 #pragma unroll
           for (int x = 0; x < N; ++x) {
             if (9 * (PLANE ? 0 : cls(z)) + 3 * cls(y) + cls(x) != e) continue;
-            double* p = out_ + pos(gen, z, y, x);
-            if constexpr (DET) *p += static_cast<double>(u[z][y][x]);  // the only writer at this moment
-            else atomicAdd(p, static_cast<double>(u[z][y][x]));
+            atomicAdd(out_ + pos(gen, z, y, x), static_cast<double>(u[z][y][x]));
           }
     }
   };
@@ -806,9 +829,10 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
     if (PLANE && any_hang) scatter_with(std::true_type{});
     else scatter_with(std::false_type{});
   };
-  if constexpr (DET) {  // one cell at a time, in cell order
-    for (int c = c0; c < c1; ++c) {
-      if (ok && cell == c) scatter();
+  if constexpr (DET) {  // phase by phase: every DoF's sum in one order
+    const int phases = meta[c0].loc[META_PHASES], mine = M->loc[META_PHASE];
+    for (int p = 0; p < phases; ++p) {
+      if (ok && mine == p) scatter();
       __syncthreads();
     }
   } else {
