@@ -444,6 +444,85 @@ struct CellLayout {
   static constexpr int WAVES_PER_EU_DET = K <= 4 ? 4 : 2;  // (no spills)
 };
 
+// Stage a batch's DoFs in LDS, CH at a time per thread so that their loads
+// overlap; threads past the end repeat the last entry instead of branching.
+// Behind them the zero block.
+template <int K, int CH, typename S, typename T>
+__device__ __forceinline__ void stage_batch(const int32_t* __restrict__ sh, int nsh, int nex, const S* __restrict__ src,
+                                            int64_t ex0, int nv, int v, int zb, T* in_) {
+  const int bt = blockDim.x, tid = threadIdx.x;
+  for (int i0 = tid; i0 < nsh; i0 += bt * CH) {
+    int at[CH];
+    int32_t gi[CH];
+    T val[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) at[q] = min(i0 + q * bt, nsh - 1);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) gi[q] = sh[at[q]];
+#pragma unroll
+    for (int q = 0; q < CH; ++q)
+      val[q] = load_as<T>(src[static_cast<uint64_t>(static_cast<uint32_t>(gi[q])) * nv + v]);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) in_[at[q]] = val[q];
+  }
+  const S* ex = src + ex0 * nv + v;
+  for (int i0 = tid; i0 < nex; i0 += bt * CH) {
+    int at[CH];
+    T val[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) at[q] = min(i0 + q * bt, nex - 1);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) val[q] = load_as<T>(ex[at[q] * nv]);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) in_[nsh + at[q]] = val[q];
+  }
+  for (int i = tid; i < batch_zero_entries(K); i += bt) in_[zb + i] = T(0);
+}
+
+// Write back: the shared DoFs' sums atomically into dst or the accumulator,
+// or as one contiguous range of partial sums (the batch's part of the
+// partial buffer); exclusive DoFs in place, with the fused step (its operands
+// loaded before the first of them is stored)
+template <typename S, typename T, int FK>
+__device__ __forceinline__ void write_batch(const int32_t* __restrict__ sh, int sh0, int nsh, int nex, int64_t ex0,
+                                            int nv, int v, const double* out_, T* __restrict__ partial,
+                                            T* __restrict__ dst, const FusedStep& fs) {
+  const int bt = blockDim.x, tid = threadIdx.x;
+  constexpr int WB = base_kind(FK) == FUSE_NONE ? 4 : 2;
+  auto put_shared = [&](int i, int32_t g, double t) {
+    if constexpr ((FK & FUSE_ATOMIC) != 0)
+      unsafeAtomicAdd(&(base_kind(FK) == FUSE_NONE ? dst : partial)[g], static_cast<T>(t));
+    else partial[static_cast<int64_t>(sh0 + i) * nv + v] = static_cast<T>(t);
+  };
+  auto index_of = [&](int i) { return (FK & FUSE_ATOMIC) != 0 ? sh[i] : 0; };
+  int i0 = tid;
+  for (; i0 + bt * (WB - 1) < nsh; i0 += bt * WB) {
+    int32_t gi[WB];
+    double t[WB];
+#pragma unroll
+    for (int q = 0; q < WB; ++q) {
+      gi[q] = index_of(i0 + q * bt);
+      t[q] = out_[i0 + q * bt];
+    }
+#pragma unroll
+    for (int q = 0; q < WB; ++q) put_shared(i0 + q * bt, gi[q], t[q]);
+  }
+  for (; i0 < nsh; i0 += bt) put_shared(i0, index_of(i0), out_[i0]);
+  const double* oex = out_ + nsh;
+  for (i0 = tid; i0 + bt * (WB - 1) < nex; i0 += bt * WB) {
+    FinishIn<S, T, FK> in[WB];
+    double t[WB];
+#pragma unroll
+    for (int q = 0; q < WB; ++q) {
+      in[q].load(fs, ex0 + i0 + q * bt, (ex0 + i0 + q * bt) * nv + v);
+      t[q] = oex[i0 + q * bt];
+    }
+#pragma unroll
+    for (int q = 0; q < WB; ++q) in[q].store(fs, (ex0 + i0 + q * bt) * nv + v, static_cast<T>(t[q]), dst);
+  }
+  for (; i0 < nex; i0 += bt) finish_dof<S, T, FK>(fs, ex0 + i0, nv, v, static_cast<T>(oex[i0]), dst);
+}
+
 // An opaque copy of the tables' address: their scalar loads stay in the phase
 // that uses them (all tables at once do not fit the scalar registers)
 template <typename P>
@@ -878,6 +957,196 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
   for (; i0 < nex; i0 += bt) finish_dof<S, T, FK>(fs, ex0 + i0, nv, v, static_cast<T>(oex[i0]), dst);
 }
 
+// The same with one lane per line of nodes and a wavefront per cell, for levels
+// of degree 5 and 6 with few batches, where a batch's latency is all that
+// counts: a lane of the plane kernel works through 36 or 49 values, and a batch
+// is staged by the 64 or 128 threads that its 8 to 16 cells take; a lane here
+// works through 6 or 7 values, turned between the axes through LDS (4 times,
+// with hanging nodes 8 times).  Registers for two blocks of 16 wavefronts per
+// CU.  One FP64 vector, lines against planes (and one lane per line in the
+// Gauss-Lobatto basis): Q6, 104 batches 13.3 us, 21.1 us (13.8 us), 589 batches
+// 19.2, 22.5 (22.5); Q5, about 140 batches 13.5, 15.1 (15.7).
+template <int K>
+struct LineLayout {
+  static constexpr int N = K + 1, RS = N | 1, CELL = N * N * RS;  // exchange rows of odd length
+  static constexpr int MAX_CELLS = batch_max_cells_hard(K), MAX_THREADS = 64 * MAX_CELLS;
+  // batches x vectors up to which lines are the better ones: Q5 480 (one FP32
+  // vector) 18.9 us by lines, 20.2 us by planes, 592 (8 vectors) 30.6, 25.7; Q6
+  // 589 see above, 704 (8 FP32 vectors) 26.7, 24.2
+  static constexpr int MOST_BLOCKS = K == 5 ? 512 : 640;
+};
+
+template <int K, typename S, typename T, int FK, bool DET>
+__global__ void __launch_bounds__(LineLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(8)))
+    vmult_line_kernel(const CellMeta* __restrict__ meta, const int32_t* __restrict__ bcell,
+                      const int32_t* __restrict__ bsh, const int32_t* __restrict__ bex,
+                      const int32_t* __restrict__ sh_idx, int nb, int run, int64_t n_shared, int zb, double h0,
+                      const EigTab<CellReal, K + 1>* __restrict__ tab, const S* __restrict__ src, T* __restrict__ partial, T* __restrict__ dst,
+                      int nv, FusedStep fs) {
+  using Y = LineLayout<K>;
+  using C = CellReal;
+  constexpr int N = Y::N, KM = K - 1, RS = Y::RS;
+  extern __shared__ __align__(16) char lds_raw[];
+  T* in_ = reinterpret_cast<T*>(lds_raw);
+  double* out_ = reinterpret_cast<double*>(lds_raw);
+  if constexpr ((FK & FUSE_ATOMIC) != 0) nv = 1;
+  const int jb = static_cast<int>(blockIdx.x / 8), bj = jb / nv, v = jb - bj * nv;  // (as in the plane kernel)
+  const int b = (bj / run * 8 + static_cast<int>(blockIdx.x % 8)) * run + bj % run;
+  if (b >= nb) return;  // (whole block)
+  const int c0 = bcell[b], c1 = bcell[b + 1];
+  const int sh0 = bsh[b], nsh = bsh[b + 1] - sh0, nex = bex[b + 1] - bex[b];
+  const int64_t ex0 = n_shared + bex[b];
+  const int bt = blockDim.x, tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const bool busy = c0 + wave < c1;  // (one cell per wavefront)
+  const CellMeta* M = meta + (busy ? c0 + wave : c0);
+  const uint32_t mk = M->mask;
+  const bool hang = mask_hanging(mk);
+  // lane (a, b): z-line x = a, y = b; y-line x = a, z = b; x-line y = a, z = b
+  // (the spare lanes repeat the last one)
+  const bool on = lane < N * N;
+  const int t = on ? lane : N * N - 1, la = t % N, lb = t / N;
+  const C lab = tab->lam[la] + tab->lam[lb];
+  // positions of the z-line's nodes: first, inner ones (start and stride), last
+  int p0, p1, pm, sz;
+  {
+    const int cx = la == 0 ? 0 : la == K ? 2 : 1, cy = lb == 0 ? 0 : lb == K ? 2 : 1;
+    const bool ex = cx == 1, ey = cy == 1;
+    int r[3] = {0, 1, 2}, sg[3] = {1, 1, 1};
+    if (hang) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        r[d] = op_axis(mk, d);
+        sg[d] = mask_sub(mk, d) ? -1 : 1;
+      }
+    }
+    auto over = [&](bool e, int a, int d) { return e && r[a] < r[d] ? KM : 1; };  // axis a runs faster than d
+    const int sx = sg[0] * over(ey, 1, 0), sy = sg[1] * over(ex, 0, 1);
+    const int oe = (ex ? (la - 1) * sx : 0) + (ey ? (lb - 1) * sy : 0);
+    const int om = (ex ? (la - 1) * sx * over(true, 2, 0) : 0) + (ey ? (lb - 1) * sy * over(true, 2, 1) : 0);
+    const uint16_t* L = M->loc + 3 * cy + cx;
+    p0 = L[0] + oe;
+    pm = L[10] + om;
+    p1 = L[20] + oe;
+    sz = sg[2] * over(ex, 0, 2) * over(ey, 1, 2);
+  }
+  auto pos = [&](int z) { return z == 0 ? p0 : z == K ? p1 : pm + (z - 1) * sz; };
+  stage_batch<K, 8>(sh_idx + sh0, nsh, nex, src, ex0, nv, v, zb, in_);
+  __syncthreads();
+  C u[N];
+  if (busy) {
+#pragma unroll
+    for (int z = 0; z < N; ++z) u[z] = static_cast<C>(in_[pos(z)]);
+  }
+  __syncthreads();  // the staged input is no longer needed
+  if (busy) {
+    C* X = out_ + wave * Y::CELL;
+    const WaveSync sync{};
+    const auto* tp = here(tab);
+    using X_ = std::integral_constant<int, 0>;
+    using Y_ = std::integral_constant<int, 1>;
+    using Z_ = std::integral_constant<int, 2>;
+    auto at = [&](auto d, int r) {
+      return decltype(d)::value == 0 ? (lb * N + la) * RS + r
+             : decltype(d)::value == 1 ? (lb * N + r) * RS + la : (r * N + lb) * RS + la;
+    };
+    auto turn = [&](auto from, auto to) {
+#pragma unroll
+      for (int r = 0; r < N; ++r) X[at(from, r)] = u[r];
+      sync();
+#pragma unroll
+      for (int r = 0; r < N; ++r) u[r] = X[at(to, r)];
+      sync();
+    };
+    const C h = static_cast<C>(ldexp(h0, -op_level(mk)) * static_cast<double>(mask_coef(mk)));
+    auto scale = [&]() {
+#pragma unroll
+      for (int r = 0; r < N; ++r) u[r] *= h * (tp->lam[r] + lab);
+    };
+    if (!hang) {
+      to_modes<N, C>(tp, u);
+      turn(Z_{}, Y_{});
+      to_modes<N, C>(tp, u);
+      turn(Y_{}, X_{});
+      to_modes<N, C>(tp, u);
+      scale();
+      from_modes<N, C>(tp, u);
+      turn(X_{}, Y_{});
+      from_modes<N, C>(tp, u);
+      turn(Y_{}, Z_{});
+      from_modes<N, C>(tp, u);
+    } else {
+      const HangBits hb(mk);
+      auto half = [&](auto d, auto trans) {  // (half_line, its table loaded row by row)
+        constexpr bool TR = decltype(trans)::value;
+        const bool set = hb.line(decltype(d)::value, la == 0, lb == 0);
+        C w[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) w[i] = i == 0 ? u[0] : C(0);
+#pragma unroll
+        for (int i = 1; i < N; ++i) {
+          const auto* H = &here(tab)->H[i * N];
+#pragma unroll
+          for (int j = 0; j < N; ++j) {
+            if constexpr (TR) w[j] += H[j] * u[i];
+            else w[i] += H[j] * u[j];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) u[i] = set ? w[i] : u[i];
+      };
+      half(Z_{}, std::false_type{});
+      turn(Z_{}, Y_{});
+      half(Y_{}, std::false_type{});
+      turn(Y_{}, X_{});
+      half(X_{}, std::false_type{});
+      to_modes<N, C>(tp, u);
+      turn(X_{}, Y_{});
+      to_modes<N, C>(tp, u);
+      turn(Y_{}, Z_{});
+      to_modes<N, C>(tp, u);
+      scale();
+      from_modes<N, C>(tp, u);
+      turn(Z_{}, Y_{});
+      from_modes<N, C>(tp, u);
+      turn(Y_{}, X_{});
+      from_modes<N, C>(tp, u);
+      half(X_{}, std::true_type{});
+      turn(X_{}, Y_{});
+      half(Y_{}, std::true_type{});
+      turn(Y_{}, Z_{});
+      half(Z_{}, std::true_type{});
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < (nsh + nex + 1) / 2; i += bt) reinterpret_cast<double2*>(out_)[i] = double2{0.0, 0.0};
+  __syncthreads();
+  if constexpr (DET) {  // phase by phase (as in the plane kernel)
+    const int phases = meta[c0].loc[META_PHASES], mine = M->loc[META_PHASE];
+    for (int p = 0; p < phases; ++p) {
+      if (busy && on && mine == p) {
+        double old[N];
+#pragma unroll
+        for (int z = 0; z < N; ++z) old[z] = out_[min(pos(z), zb)];
+#pragma unroll
+        for (int z = 0; z < N; ++z) out_[min(pos(z), zb)] = old[z] + static_cast<double>(u[z]);
+      }
+      __syncthreads();
+    }
+  } else {
+    if (busy && on) {
+      if (p0 < zb) atomicAdd(out_ + p0, static_cast<double>(u[0]));
+      if (p1 < zb) atomicAdd(out_ + p1, static_cast<double>(u[K]));
+      if (pm < zb) {
+#pragma unroll
+        for (int z = 1; z < K; ++z) atomicAdd(out_ + pos(z), static_cast<double>(u[z]));
+      }
+    }
+    __syncthreads();
+  }
+  write_batch<S, T, FK>(sh_idx + sh0, sh0, nsh, nex, ex0, nv, v, out_, partial, dst, fs);
+}
+
 template <typename T>
 __global__ void clear_shared_kernel(int64_t n, T* __restrict__ dst) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
@@ -996,9 +1265,22 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
     // step of 8 vectors 5 %, the others nothing)
     const int64_t run = std::max<int64_t>(1, std::min<int64_t>(4, nb / 64));
     const int64_t blocks = 8 * run * ((nb + 8 * run - 1) / (8 * run)) * nv;
-    vmult_batch_kernel<K, S, T, FK, DET><<<static_cast<unsigned>(blocks), 64 * waves, lds, s>>>(
-        c.meta, c.batch_cell, c.batch_sh, c.batch_ex, c.sh_idx, static_cast<int>(nb), static_cast<int>(run), c.n_shared, c.max_batch_dofs, c.h0, tab,
-        static_cast<const S*>(src), sums, static_cast<T*>(dst), nv, f);
+    auto launch = [&](auto kernel, int wavefronts, size_t bytes) {
+      kernel<<<static_cast<unsigned>(blocks), 64 * wavefronts, bytes, s>>>(
+          c.meta, c.batch_cell, c.batch_sh, c.batch_ex, c.sh_idx, static_cast<int>(nb), static_cast<int>(run), c.n_shared,
+          c.max_batch_dofs, c.h0, tab, static_cast<const S*>(src), sums, static_cast<T*>(dst), nv, f);
+    };
+    // levels with few batches take a line per lane (see vmult_line_kernel)
+    bool lines = false;
+    if constexpr (K >= 5) lines = nb * nv <= LineLayout<K>::MOST_BLOCKS;
+    if constexpr (K >= 5) {
+      using Z = LineLayout<K>;
+      MFMG_REQUIRE(c.max_batch_cells <= Z::MAX_CELLS, MFMG_ERR_INVALID_ARG, "batch exceeds the operator's block");
+      if (lines)
+        launch(&vmult_line_kernel<K, S, T, FK, DET>, c.max_batch_cells,
+               std::max(lds, static_cast<size_t>(c.max_batch_cells) * Z::CELL * sizeof(C)));
+    }
+    if (!lines) launch(&vmult_batch_kernel<K, S, T, FK, DET>, waves, lds);
   }
   check_launch();
   if constexpr (atom && !into_dst) {
