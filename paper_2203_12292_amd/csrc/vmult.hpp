@@ -439,9 +439,19 @@ struct CellLayout {
   static constexpr int CHUNK = K <= 4 ? 8 : K == 5 ? 10 : 20;
   // wavefronts per SIMD the registers are cut to: as many as the LDS of the
   // usual batches lets run (Q4 FP64: 4 0.446 ms, 5 0.422 ms; a Q3 smoothing
-  // step of 8 FP32 vectors: 4 3.16 ms, 8 2.94 ms)
-  static constexpr int WAVES_PER_EU = K <= 2 ? 4 : K == 3 ? 8 : K == 4 ? 5 : 2;
-  static constexpr int WAVES_PER_EU_DET = K <= 4 ? 4 : 2;  // (no spills)
+  // step of 8 FP32 vectors: 4 3.16 ms, 8 2.94 ms).  The deterministic mode: no
+  // spills.
+  template <bool DET, bool SKIP>
+  static constexpr int waves_per_eu() {
+    if (DET) return K <= 4 ? 4 : 2;
+    return K <= 2 ? 4 : K == 3 ? 8 : K == 4 ? 5 : SKIP ? 3 : 2;
+  }
+  // Wavefronts past a batch's cells (the block fits the level's largest batch)
+  // work on zeros, or with SKIP on nothing.  Q6: two wavefronts for batches of
+  // 8 cells, where a few at the boundary have up to 16 (3.7M DoFs, 3 FP64
+  // vectors 114 us, skipping 94 us); where all have cells the branch costs up
+  // to 5 %.
+  static constexpr bool skip(int waves) { return K == 6 && waves > 1; }
 };
 
 // Stage a batch's DoFs in LDS, CH at a time per thread so that their loads
@@ -533,8 +543,8 @@ __device__ __forceinline__ const __attribute__((address_space(4))) P* here(const
   return c;
 }
 
-template <int K, typename S, typename T, int FK, bool DET>
-__global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(DET ? CellLayout<K>::WAVES_PER_EU_DET : CellLayout<K>::WAVES_PER_EU)))
+template <int K, typename S, typename T, int FK, bool DET, bool SKIP>
+__global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(CellLayout<K>::template waves_per_eu<DET, SKIP>())))
     vmult_batch_kernel(const CellMeta* __restrict__ meta, const int32_t* __restrict__ bcell,
                       const int32_t* __restrict__ bsh, const int32_t* __restrict__ bex,
                       const int32_t* __restrict__ sh_idx, int nb, int run, int64_t n_shared, int zb, double h0,
@@ -568,6 +578,8 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
   const int lc = lane / LPC, zl = lane - lc * LPC;
   const int cell = c0 + wave * Y::CPW + lc;
   const bool ok = lc < Y::CPW && cell < c1;
+  // SKIP: a wavefront past the batch's cells only stages and writes back
+  const bool busy = !SKIP || c0 + __builtin_amdgcn_readfirstlane(wave) * Y::CPW < c1;
   // the cell's record: its mask and the local entity starts of this lane's
   // plane (or of the cell), absent ones at the zero block
   const CellMeta* M = meta + (ok ? cell : c0);
@@ -675,8 +687,10 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
         for (int x = 0; x < N; ++x) u[z][y][x] = static_cast<C>(in_[pos(gen, z, y, x)]);
   };
   __syncthreads();
-  if (PLANE && any_hang) gather(std::true_type{});
-  else gather(std::false_type{});
+  if (busy) {
+    if (PLANE && any_hang) gather(std::true_type{});
+    else gather(std::false_type{});
+  }
   __syncthreads();  // the staged input is no longer needed
 
   // exchange buffer of this lane's cell, in the place of the input
@@ -762,100 +776,102 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
     }
   };
 
-  if (any_hang) interpolate(std::false_type{});
-  // to modes along x and y
-  const auto* tp = here(tab);
+  if (busy) {
+    if (any_hang) interpolate(std::false_type{});
+    // to modes along x and y
+    const auto* tp = here(tab);
 #pragma unroll
-  for (int z = 0; z < NZ; ++z) {
+    for (int z = 0; z < NZ; ++z) {
 #pragma unroll
-    for (int y = 0; y < N; ++y) to_modes<N, C>(tp, u[z][y]);
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-      C w[N];
-#pragma unroll
-      for (int y = 0; y < N; ++y) w[y] = u[z][y][x];
-      to_modes<N, C>(tp, w);
-#pragma unroll
-      for (int y = 0; y < N; ++y) u[z][y][x] = w[y];
-    }
-  }
-  const C h = static_cast<C>(ldexp(h0, -op_level(mk)) * static_cast<double>(mask_coef(mk)));
-  if constexpr (PLANE) {
-    // lane z holds modes (x, y) of its plane; lane j takes the z-lines of y-mode j
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-#pragma unroll
-      for (int y = 0; y < N; ++y) X[zl * RS + y] = u[0][y][x];
-      sync();
-#pragma unroll
-      for (int z = 0; z < N; ++z) u[0][z][x] = X[z * RS + zl];
-      sync();
-    }
-    const auto* tz = here(tab);
-    C lj = tz->lam[0];
-#pragma unroll
-    for (int j = 1; j < N; ++j) lj = zl == j ? tz->lam[j] : lj;
-    C a[N];  // h (L_j + L_z)
-#pragma unroll
-    for (int z = 0; z < N; ++z) a[z] = h * tz->lam[z] + h * lj;
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-      const C hx = h * tz->lam[x];
-      C w[N];
-#pragma unroll
-      for (int z = 0; z < N; ++z) w[z] = u[0][z][x];
-      to_modes<N, C>(tz, w);
-#pragma unroll
-      for (int z = 0; z < N; ++z) w[z] *= a[z] + hx;
-      from_modes<N, C>(tz, w);
-#pragma unroll
-      for (int z = 0; z < N; ++z) u[0][z][x] = w[z];
-    }
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-#pragma unroll
-      for (int z = 0; z < N; ++z) X[z * RS + zl] = u[0][z][x];
-      sync();
-#pragma unroll
-      for (int y = 0; y < N; ++y) u[0][y][x] = X[zl * RS + y];
-      sync();
-    }
-  } else {
-    C a[N];
-#pragma unroll
-    for (int z = 0; z < N; ++z) a[z] = h * tp->lam[z];
-#pragma unroll
-    for (int y = 0; y < N; ++y)
+      for (int y = 0; y < N; ++y) to_modes<N, C>(tp, u[z][y]);
 #pragma unroll
       for (int x = 0; x < N; ++x) {
         C w[N];
 #pragma unroll
-        for (int z = 0; z < N; ++z) w[z] = u[z][y][x];
+        for (int y = 0; y < N; ++y) w[y] = u[z][y][x];
         to_modes<N, C>(tp, w);
 #pragma unroll
-        for (int z = 0; z < N; ++z) w[z] *= a[z] + h * (tp->lam[x] + tp->lam[y]);
+        for (int y = 0; y < N; ++y) u[z][y][x] = w[y];
+      }
+    }
+    const C h = static_cast<C>(ldexp(h0, -op_level(mk)) * static_cast<double>(mask_coef(mk)));
+    if constexpr (PLANE) {
+      // lane z holds modes (x, y) of its plane; lane j takes the z-lines of y-mode j
+#pragma unroll
+      for (int x = 0; x < N; ++x) {
+#pragma unroll
+        for (int y = 0; y < N; ++y) X[zl * RS + y] = u[0][y][x];
+        sync();
+#pragma unroll
+        for (int z = 0; z < N; ++z) u[0][z][x] = X[z * RS + zl];
+        sync();
+      }
+      const auto* tz = here(tab);
+      C lj = tz->lam[0];
+#pragma unroll
+      for (int j = 1; j < N; ++j) lj = zl == j ? tz->lam[j] : lj;
+      C a[N];  // h (L_j + L_z)
+#pragma unroll
+      for (int z = 0; z < N; ++z) a[z] = h * tz->lam[z] + h * lj;
+#pragma unroll
+      for (int x = 0; x < N; ++x) {
+        const C hx = h * tz->lam[x];
+        C w[N];
+#pragma unroll
+        for (int z = 0; z < N; ++z) w[z] = u[0][z][x];
+        to_modes<N, C>(tz, w);
+#pragma unroll
+        for (int z = 0; z < N; ++z) w[z] *= a[z] + hx;
+        from_modes<N, C>(tz, w);
+#pragma unroll
+        for (int z = 0; z < N; ++z) u[0][z][x] = w[z];
+      }
+#pragma unroll
+      for (int x = 0; x < N; ++x) {
+#pragma unroll
+        for (int z = 0; z < N; ++z) X[z * RS + zl] = u[0][z][x];
+        sync();
+#pragma unroll
+        for (int y = 0; y < N; ++y) u[0][y][x] = X[zl * RS + y];
+        sync();
+      }
+    } else {
+      C a[N];
+#pragma unroll
+      for (int z = 0; z < N; ++z) a[z] = h * tp->lam[z];
+#pragma unroll
+      for (int y = 0; y < N; ++y)
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+          C w[N];
+#pragma unroll
+          for (int z = 0; z < N; ++z) w[z] = u[z][y][x];
+          to_modes<N, C>(tp, w);
+#pragma unroll
+          for (int z = 0; z < N; ++z) w[z] *= a[z] + h * (tp->lam[x] + tp->lam[y]);
+          from_modes<N, C>(tp, w);
+#pragma unroll
+          for (int z = 0; z < N; ++z) u[z][y][x] = w[z];
+        }
+    }
+    tp = here(tab);
+    // back to nodes along y and x
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+#pragma unroll
+      for (int x = 0; x < N; ++x) {
+        C w[N];
+#pragma unroll
+        for (int y = 0; y < N; ++y) w[y] = u[z][y][x];
         from_modes<N, C>(tp, w);
 #pragma unroll
-        for (int z = 0; z < N; ++z) u[z][y][x] = w[z];
+        for (int y = 0; y < N; ++y) u[z][y][x] = w[y];
       }
-  }
-  tp = here(tab);
-  // back to nodes along y and x
 #pragma unroll
-  for (int z = 0; z < NZ; ++z) {
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-      C w[N];
-#pragma unroll
-      for (int y = 0; y < N; ++y) w[y] = u[z][y][x];
-      from_modes<N, C>(tp, w);
-#pragma unroll
-      for (int y = 0; y < N; ++y) u[z][y][x] = w[y];
+      for (int y = 0; y < N; ++y) from_modes<N, C>(tp, u[z][y]);
     }
-#pragma unroll
-    for (int y = 0; y < N; ++y) from_modes<N, C>(tp, u[z][y]);
+    if (any_hang) interpolate(std::true_type{});
   }
-  if (any_hang) interpolate(std::true_type{});
 
   if constexpr (!PLANE) {
 #pragma unroll
@@ -915,7 +931,7 @@ __global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amd
       __syncthreads();
     }
   } else {
-    scatter();
+    if (busy) scatter();
     __syncthreads();
   }
   // write back: the shared DoFs' sums atomically into dst or the accumulator,
@@ -1280,7 +1296,10 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
         launch(&vmult_line_kernel<K, S, T, FK, DET>, c.max_batch_cells,
                std::max(lds, static_cast<size_t>(c.max_batch_cells) * Z::CELL * sizeof(C)));
     }
-    if (!lines) launch(&vmult_batch_kernel<K, S, T, FK, DET>, waves, lds);
+    if (!lines) {  // (degree 6: instantiated with and without SKIP)
+      if (K == 6 && waves > 1) launch(&vmult_batch_kernel<K, S, T, FK, DET, Y::skip(2)>, waves, lds);
+      else launch(&vmult_batch_kernel<K, S, T, FK, DET, Y::skip(1)>, waves, lds);
+    }
   }
   check_launch();
   if constexpr (atom && !into_dst) {
