@@ -438,20 +438,29 @@ struct CellLayout {
   // the usual batch (Q6, 8 FP32 vectors: 10 at a time 3.48 ms, 20 3.38 ms)
   static constexpr int CHUNK = K <= 4 ? 8 : K == 5 ? 10 : 20;
   // wavefronts per SIMD the registers are cut to: as many as the LDS of the
-  // usual batches lets run (Q4 FP64: 4 0.446 ms, 5 0.422 ms; a Q3 smoothing
-  // step of 8 FP32 vectors: 4 3.16 ms, 8 2.94 ms).  The deterministic mode: no
-  // spills.
-  template <bool DET, bool SKIP>
+  // usual batches lets run (Q4 FP64: 4 0.446 ms, 5 0.422 ms), if they spill
+  // little.  Q3: 8 leave 39 registers of a fused FP64 step in scratch (a
+  // smoothing step on 270,000 cells 500 us, with 6 360 us, with 5 307 us), and
+  // 5 is no worse for FP64 vectors and fused FP32 steps anywhere; only the
+  // plain operator on FP32 vectors gains from 8 where most cells have hanging
+  // nodes (a smoothing step of 8 vectors on 306,536 cells 2.83 ms, with 5 3.01 ms).
+  // The deterministic mode: no spills.
+  template <typename T, int FK, bool DET, bool SKIP>
   static constexpr int waves_per_eu() {
     if (DET) return K <= 4 ? 4 : 2;
-    return K <= 2 ? 4 : K == 3 ? 8 : K == 4 ? 5 : SKIP ? 3 : 2;
+    if (K == 3) return sizeof(T) == 4 && base_kind(FK) == FUSE_NONE ? 8 : 5;
+    return K <= 2 ? 4 : K == 4 ? 5 : SKIP ? 3 : 2;
   }
   // Wavefronts past a batch's cells (the block fits the level's largest batch)
   // work on zeros, or with SKIP on nothing.  Q6: two wavefronts for batches of
-  // 8 cells, where a few at the boundary have up to 16 (3.7M DoFs, 3 FP64
-  // vectors 114 us, skipping 94 us); where all have cells the branch costs up
-  // to 5 %.
-  static constexpr bool skip(int waves) { return K == 6 && waves > 1; }
+  // 8 cells, where a few at the boundary have up to 16 (15,163 cells, 3 FP64
+  // vectors 114 us, skipping 95 us); where all have cells the branch costs up
+  // to 5 %.  Q3: one or two of 8 to 10 (270,000 cells, 3 FP64 vectors 231 us,
+  // skipping 194 us).
+  template <typename T, int FK>
+  static constexpr bool skip(int waves) {
+    return (K == 6 && waves > 1) || (K == 3 && !(sizeof(T) == 4 && base_kind(FK) == FUSE_NONE));
+  }
 };
 
 // Stage a batch's DoFs in LDS, CH at a time per thread so that their loads
@@ -544,7 +553,7 @@ __device__ __forceinline__ const __attribute__((address_space(4))) P* here(const
 }
 
 template <int K, typename S, typename T, int FK, bool DET, bool SKIP>
-__global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(CellLayout<K>::template waves_per_eu<DET, SKIP>())))
+__global__ void __launch_bounds__(CellLayout<K>::MAX_THREADS) __attribute__((amdgpu_waves_per_eu(CellLayout<K>::template waves_per_eu<T, FK, DET, SKIP>())))
     vmult_batch_kernel(const CellMeta* __restrict__ meta, const int32_t* __restrict__ bcell,
                       const int32_t* __restrict__ bsh, const int32_t* __restrict__ bex,
                       const int32_t* __restrict__ sh_idx, int nb, int run, int64_t n_shared, int zb, double h0,
@@ -1297,8 +1306,8 @@ void vmult_run(const CellView& c, int nv, void* dst, const void* src, const Fuse
                std::max(lds, static_cast<size_t>(c.max_batch_cells) * Z::CELL * sizeof(C)));
     }
     if (!lines) {  // (degree 6: instantiated with and without SKIP)
-      if (K == 6 && waves > 1) launch(&vmult_batch_kernel<K, S, T, FK, DET, Y::skip(2)>, waves, lds);
-      else launch(&vmult_batch_kernel<K, S, T, FK, DET, Y::skip(1)>, waves, lds);
+      if (K == 6 && waves > 1) launch(&vmult_batch_kernel<K, S, T, FK, DET, Y::template skip<T, FK>(2)>, waves, lds);
+      else launch(&vmult_batch_kernel<K, S, T, FK, DET, Y::template skip<T, FK>(1)>, waves, lds);
     }
   }
   check_launch();
