@@ -200,42 +200,66 @@ void upload_into(DeviceArray<T>& d, const std::vector<T>& h) { d.upload(h); }
 }  // namespace
 
 namespace {
-// The operator's record of an axis-aligned cell: its entities in the cell's own
-// order, or for a cell with hanging nodes reflected and permuted (slots.hpp).
-// An entity starts at the node that comes first in the record's order.  zb:
-// start of the zero block, for absent entities.
-CellMeta oriented_record(const LevelDofs& H, int64_t c, int zb) {
+// How the entities of an axis-aligned cell come in the operator's record: in the
+// cell's own order, or for a cell with hanging nodes reflected and permuted
+// (slots.hpp).  An entity starts at the node that comes first in the record's
+// order.  One entry per axis order and set of reflected axes.
+struct Orientation {
+  uint8_t slot[N_SLOTS];   // the cell's own slot of each of the record's entities
+  uint16_t first[N_SLOTS]; // the offset of its first node
+};
+constexpr int AXIS_ORDERS[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
+
+std::vector<Orientation> orientations(int k) {
+  std::vector<Orientation> tab(6 * 8);
+  const int km = k - 1;
+  for (int o = 0; o < 6; ++o)
+    for (int flips = 0; flips < 8; ++flips)  // (by the cell's own axes)
+      for (int e = 0; e < N_SLOTS; ++e) {
+        const int cls[3] = {e % 3, (e / 3) % 3, e / 9};  // classes along the record's axes: 0, inner, k
+        int own[3];
+        for (int d = 0; d < 3; ++d) {
+          const int a = AXIS_ORDERS[o][d];
+          own[a] = (flips >> a & 1) ? 2 - cls[d] : cls[d];
+        }
+        int first = 0, stride = 1;
+        for (int a = 0; a < 3; ++a)
+          if (own[a] == 1) {
+            if ((flips >> a & 1) && km > 1) first += (km - 1) * stride;
+            stride *= km;
+          }
+        tab[o * 8 + flips].slot[e] = static_cast<uint8_t>(node_slot(own[0], own[1], own[2], 2));
+        tab[o * 8 + flips].first[e] = static_cast<uint16_t>(first);
+      }
+  return tab;
+}
+
+// zb: start of the zero block, for absent entities
+CellMeta oriented_record(const LevelDofs& H, const std::vector<Orientation>& tab, int64_t c, int zb) {
   const uint32_t m = H.mask[c];
-  const int km = H.k - 1;
-  int axis[3] = {0, 1, 2};
-  bool flip[3] = {false, false, false};  // by the cell's own axis
   CellMeta M{};
   M.mask = (m & (MASK_COEF_BITS | 0x1f0000u));
+  int order = 0, flips = 0;
   if (mask_hanging(m)) {
-    // hanging faces first, then hanging edges
-    std::stable_sort(axis, axis + 3, [&](int a, int b) {
-      return 2 * mask_face(m, a) + mask_edge(m, a) > 2 * mask_face(m, b) + mask_edge(m, b);
-    });
+    // hanging faces first, then hanging edges, else in axis order
+    int rank[3];
+    for (int a = 0; a < 3; ++a) rank[a] = 2 * mask_face(m, a) + mask_edge(m, a);
+    const int lead = rank[0] >= rank[1] && rank[0] >= rank[2] ? 0 : rank[1] >= rank[2] ? 1 : 2;
+    const int p = lead == 0 ? 1 : 0, q = lead == 2 ? 1 : 2;  // the other two
+    order = 2 * lead + (rank[p] >= rank[q] ? 0 : 1);
+    flips = static_cast<int>(m & 7u);
     for (int d = 0; d < 3; ++d) {
-      flip[axis[d]] = mask_sub(m, axis[d]) != 0;
-      M.mask |= static_cast<uint32_t>(mask_sub(m, axis[d])) << d | static_cast<uint32_t>(mask_face(m, axis[d])) << (3 + d) |
-                static_cast<uint32_t>(mask_edge(m, axis[d])) << (6 + d);
+      const int a = AXIS_ORDERS[order][d];
+      M.mask |= static_cast<uint32_t>(mask_sub(m, a)) << d | static_cast<uint32_t>(mask_face(m, a)) << (3 + d) |
+                static_cast<uint32_t>(mask_edge(m, a)) << (6 + d);
     }
-    const int second = axis[1] > axis[2] ? 1 : 0;  // of the two axes left, in descending order
-    M.mask |= static_cast<uint32_t>(2 * axis[0] + second) << 21;
+    M.mask |= static_cast<uint32_t>(order) << 21;
   }
+  const Orientation& o = tab[order * 8 + flips];
+  const uint16_t absent = static_cast<uint16_t>(batch_mcap(H.k));
   for (int e = 0; e < N_SLOTS; ++e) {
-    const int cls[3] = {e % 3, (e / 3) % 3, e / 9};  // classes along the record's axes: 0, inner, k
-    int own[3];
-    for (int d = 0; d < 3; ++d) own[axis[d]] = flip[axis[d]] ? 2 - cls[d] : cls[d];
-    const uint16_t l = H.loc[node_slot(own[0], own[1], own[2], 2) * H.n_cells + c];
-    int first = l == batch_mcap(H.k) ? zb : l, stride = 1;
-    for (int a = 0; a < 3; ++a)
-      if (own[a] == 1) {
-        if (flip[a] && km > 1) first += (km - 1) * stride;
-        stride *= km;
-      }
-    M.loc[10 * (e / 9) + e % 9] = static_cast<uint16_t>(first);
+    const uint16_t l = H.loc[o.slot[e] * H.n_cells + c];
+    M.loc[10 * (e / 9) + e % 9] = static_cast<uint16_t>((l == absent ? zb : l) + o.first[e]);
   }
   return M;
 }
@@ -308,9 +332,10 @@ void init_level(Context& ctx, Level& L, const LevelDofs& H, double lo, bool work
     L.view.max_batch_cells = max_cells;
     L.view.max_batch_dofs = max_dofs;
     std::vector<CellMeta> meta(H.n_cells);
+    const std::vector<Orientation> tab = orientations(H.k);
     for (int64_t c = 0; c < H.n_cells; ++c) {
       if (ctx.geo.kind == 0) {
-        meta[c] = oriented_record(H, c, max_dofs);
+        meta[c] = oriented_record(H, tab, c, max_dofs);
         continue;
       }
       CellMeta& M = meta[c];
