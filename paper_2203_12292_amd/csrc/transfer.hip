@@ -96,6 +96,7 @@ __device__ __forceinline__ void sweep(const T* __restrict__ P, const T (&x)[NI],
 }
 
 constexpr int TR_WAVES = 2;  // independent wavefronts per block
+enum { PLANES, LINES_ONE, LINES_EACH };  // how the lanes split a group: planes, or lines of one or of each vector
 
 // How a launch splits the work: `groups` transfer groups per wavefront, 2^lv
 // interleaved vectors at a time.
@@ -132,13 +133,14 @@ struct TrLds {
 // runs of whole faces and interiors ((k-1)^2 adjacent values) where the
 // planes' load covers one row of each of several groups, k-1 values apiece
 // (the same prolongation 110 us by lines, 156 us by planes at its best).
-template <int KF, int KC, int NF, typename S, typename T, bool PROLONG, bool LINES>
+template <int KF, int KC, int NF, typename S, typename T, bool PROLONG, int HOW>
 __global__ void __launch_bounds__(64 * TR_WAVES)
     transfer_kernel(const int32_t* __restrict__ fdesc, const int32_t* __restrict__ cdesc, int64_t n_groups,
                     int64_t n_blocks, int groups, int lv, TrTab<T, NF, KC + 1> tab, const S* __restrict__ src,
                     S* __restrict__ dst, int nv, bool plain) {
   constexpr int NC = KC + 1, FS = transfer_record(LatticeRows<KF, NF>::NCLS), CS = transfer_record(3);
-  constexpr bool IDENT = NF == NC && KF == KC;
+  constexpr bool IDENT = NF == NC && KF == KC, LINES = HOW != PLANES;
+  if constexpr (HOW == LINES_ONE) nv = 1;  // (the index arithmetic folds: 3 to 15 % of the time)
   using L = TrLds<NF, NC, LINES>;
   constexpr int RS = L::RS, LN = L::N;
   extern __shared__ __align__(16) char lds_raw[];
@@ -189,7 +191,8 @@ __global__ void __launch_bounds__(64 * TR_WAVES)
     const int nb = nv - v0 < vb ? nv - v0 : vb;
     const bool mine = pg < ng && pv < nb;
     auto fine_at = [&](int32_t e) {
-      return static_cast<uint64_t>(static_cast<uint32_t>(e)) * nv + (LINES ? v0 : v0 + pv);
+      if constexpr (HOW == LINES_ONE) return static_cast<int64_t>(e);
+      return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(e)) * nv + (LINES ? v0 : v0 + pv));
     };
     auto load_row = [&](const S* p, int J, T (&w)[NF]) {
       if (mine)
@@ -485,10 +488,11 @@ TrShape transfer_shape(int nv, int64_t n_groups, int bytes) {
   return s;
 }
 
-template <int KF, int KC, int NF, typename S, bool PROLONG, bool LINES>
+template <int KF, int KC, int NF, typename S, bool PROLONG, int HOW>
 void transfer_run(const int32_t* fdesc, const int32_t* cdesc, int64_t n, int nv, void* dst, const void* src,
                   bool plain, hipStream_t s) {
   using T = typename Acc<S>::type;
+  constexpr bool LINES = HOW != PLANES;
   if (n == 0) return;
   static const TrTab<T, NF, KC + 1> tab = make_trtab<T, NF, KC + 1>(KF, KC);
   const TrShape sh = transfer_shape<NF, KC + 1, LINES>(nv, n, sizeof(T));
@@ -497,7 +501,7 @@ void transfer_run(const int32_t* fdesc, const int32_t* cdesc, int64_t n, int nv,
   const int64_t blocks = (units + TR_WAVES - 1) / TR_WAVES, grid = (blocks + 7) / 8 * 8;
   constexpr int ints = transfer_record(LatticeRows<KF, NF>::NCLS) + transfer_record(3);
   const size_t lds = per_block * (ints * 4 + (TrLds<NF, KC + 1, LINES>::N << sh.lv) * sizeof(T));
-  transfer_kernel<KF, KC, NF, S, T, PROLONG, LINES><<<static_cast<unsigned>(grid), 64 * TR_WAVES, lds, s>>>(
+  transfer_kernel<KF, KC, NF, S, T, PROLONG, HOW><<<static_cast<unsigned>(grid), 64 * TR_WAVES, lds, s>>>(
       fdesc, cdesc, n, blocks, sh.groups, sh.lv, tab, static_cast<const S*>(src), static_cast<S*>(dst), nv, plain);
   check_launch();
 }
@@ -517,8 +521,9 @@ void transfer_split(const int32_t* fdesc, const int32_t* cdesc, int64_t n, int n
                     bool plain, hipStream_t s) {
   constexpr bool wide = sizeof(typename Acc<S>::type) == 8;
   constexpr int64_t most = PROLONG ? (wide ? 6000 : 8000) : std::min(5 * NF * NF * NF, wide ? 11000 : 6000);
-  if (nv == 1 || n * nv <= most) transfer_run<KF, KC, NF, S, PROLONG, true>(fdesc, cdesc, n, nv, dst, src, plain, s);
-  else transfer_run<KF, KC, NF, S, PROLONG, false>(fdesc, cdesc, n, nv, dst, src, plain, s);
+  if (nv == 1) transfer_run<KF, KC, NF, S, PROLONG, LINES_ONE>(fdesc, cdesc, n, nv, dst, src, plain, s);
+  else if (n * nv <= most) transfer_run<KF, KC, NF, S, PROLONG, LINES_EACH>(fdesc, cdesc, n, nv, dst, src, plain, s);
+  else transfer_run<KF, KC, NF, S, PROLONG, PLANES>(fdesc, cdesc, n, nv, dst, src, plain, s);
 }
 
 template <int KF, int KC, int NF, typename S>

@@ -17,7 +17,7 @@ from perf import cases
 
 pytestmark = pytest.mark.gpu
 TOL = {"vmult": {"f64": 1e-12, "f32": 5e-7, "bf16": 4e-3}, "smooth": {"f64": 1e-12, "f32": 1e-6, "bf16": 2e-2}}
-MESHES = [("ball", 2, 0, 2), ("ball", 3, 0, 2), ("ball", 4, 0, 3), ("octant", 1, 0, 5)]
+MESHES = [("ball", 2, 0, 2), ("ball", 4, 0, 3), ("octant", 1, 0, 4)]
 
 
 @pytest.mark.parametrize("mesh", MESHES)
