@@ -89,7 +89,7 @@ def _kname(name):
 # the plain FP64 Q4 operator on one vector, axis-aligned cells, default mode
 # (fused kind 4: no fused step, the shared DoFs' contributions added to the
 # output atomically) and the clearing of the output's shared DoFs before it
-_Q4_VMULT = re.compile(r"vmult_batch_kernel<4, double, double, 4(, 0)?(, false)?>$")
+_Q4_VMULT = re.compile(r"vmult_batch_kernel<4, double, double, 4(, 0)?(, false){0,2}>$")
 _Q4_CLEAR = "clear_shared_kernel<double>"
 
 

@@ -234,9 +234,10 @@ LevelDofs build_level_dofs(const Octree& tree, int k, bool dirichlet, bool want_
   MFMG_REQUIRE(ne < (1ll << 31), MFMG_ERR_UNSUPPORTED, "too many entities");
   auto esize = [&](int64_t id) { return slot_size(ents[id].slot, k); };
 
-  // batches: consecutive cells while the touched DoFs fit the LDS budget.  A
-  // block evaluates `quantum` cells at a time, so a full batch is cut back to
-  // a multiple of that many cells (the cut-off cells start the next batch).
+  // batches: consecutive cells while the touched DoFs fit the LDS budget.  On
+  // mapped cells a block evaluates `quantum` cells at a time, so a full batch is
+  // cut back to a multiple of that many (the cut-off cells start the next
+  // batch); axis-aligned cells are cut alike (see slots.hpp).
   const int mcap = batch_mcap(k);
   const int64_t quantum = BATCH_QUANTIZE ? BATCH_WAVES * cells_per_wave(k + 1) : 1;
   std::vector<int32_t> stamp(ne, -1);

@@ -56,36 +56,40 @@ __host__ __device__ constexpr int slot_size(int s, int k) {
   return s < 8 ? 1 : s < 20 ? km : s < 26 ? km * km : km * km * km;
 }
 
-// Operator kernels: a cell is handled by n^2 lanes of one wavefront (one
-// lane per line of n nodes), cells_per_wave(n) = floor(64 / n^2) cells per
-// wavefront, BATCH_WAVES wavefronts per block.
+// Operator on mapped cells: a cell is handled by n^2 lanes of one wavefront
+// (one lane per line of n nodes), cells_per_wave(n) = floor(64 / n^2) cells per
+// wavefront, BATCH_WAVES wavefronts per block.  (Axis-aligned cells: CellLayout
+// and LineLayout in vmult.hpp.)
 #ifndef MFMG_BATCH_WAVES
 #define MFMG_BATCH_WAVES 8
 #endif
 constexpr int BATCH_WAVES = MFMG_BATCH_WAVES;
 __host__ __device__ constexpr int cells_per_wave(int n) { return 64 / (n * n); }
 
-// Cell batches of the operator: a batch's DoFs are staged in LDS (input and
-// accumulated output) next to the per-wave work buffers, within
-// BATCH_LDS_BYTES per block (sized for FP64).  batch_mcap(k) bounds the DoFs a
-// batch touches.  Behind them sits a block of batch_zero_entries(k) entries:
-// zeros in the input and a discarded area in the output, where absent
-// (Dirichlet) entities and lanes without a cell point, so that gather and
-// scatter need no branches.
+// Cell batches of the operator.  The limits below are those of the kernel for
+// mapped cells: a batch's DoFs are staged in LDS (input and accumulated output)
+// next to the per-wave work buffers, within BATCH_LDS_BYTES per block (sized
+// for FP64), and batch_mcap(k) bounds the DoFs a batch touches.  The kernels
+// for axis-aligned cells need less LDS, and their wavefronts hold other numbers
+// of cells, but take the same batches: the batches determine the numbering of
+// the DoFs, which is part of what a caller sees.  Behind a batch's DoFs sits a
+// block of batch_zero_entries(k) entries, zeros in the input, where absent
+// (Dirichlet) entities and lanes without a cell point, so that the gather needs
+// no branches (mapped cells: a discarded area in the output as well).
 #ifndef MFMG_BATCH_LDS_BYTES
 #define MFMG_BATCH_LDS_BYTES 81920
 #endif
 constexpr int BATCH_LDS_BYTES = MFMG_BATCH_LDS_BYTES;
 constexpr int BATCH_MAX_CELLS = 1024;
 // From degree 5 on, the batch's cell metadata (64 B per cell) is staged in
-// LDS too, for at most two cell groups of the block per batch.
+// LDS too (mapped cells), for at most two cell groups of the block per batch.
 __host__ __device__ constexpr bool batch_meta_in_lds(int k) { return k >= 5; }
 __host__ __device__ constexpr int batch_max_cells(int k) {
   return batch_meta_in_lds(k) ? 2 * BATCH_WAVES * cells_per_wave(k + 1) : BATCH_MAX_CELLS;
 }
 // Bound on a batch's cells by degree: the operator's block has a lane (up to
 // degree 2) or k+1 lanes for each of them.  (The DoFs bound them first: the
-// largest batches met hold 560 cells at degree 2, 144 at degree 3, 48 at
+// largest batches met hold 560 cells at degree 2, 160 at degree 3, 64 at
 // degree 4.)
 __host__ __device__ constexpr int batch_max_cells_hard(int k) {
   return k <= 2 ? BATCH_MAX_CELLS : k == 3 ? 256 : k == 4 ? 96 : batch_max_cells(k);

@@ -410,10 +410,11 @@ struct HangBits {
 // instead of 10 passes of the cell's values through LDS, and one set of
 // addresses per plane instead of two per line.
 //
-// What bounds it (Q4, 67.8M FP64 DoFs, 0.42 ms against 0.78 ms by lines): its
-// HBM traffic, 2.05 GB with the clearing (vectors, repeated reads of the shared
-// DoFs, their index list and atomic adds), takes 0.44 ms at the 4.7 TB/s of a
-// plain copy; runs of 16 to 512 batches an XCD instead of 4 change nothing.  Q6 on 8
+// What bounds it (Q4, 67.8M FP64 DoFs, 0.42 to 0.50 ms on the cards measured,
+// against 0.78 ms by lines): HBM.  Its traffic, 2.05 GB with the clearing
+// (vectors, repeated reads of the shared DoFs, their index list and atomic
+// adds), goes by at 4.1 to 4.9 TB/s, where a plain copy of 4 GiB reaches
+// 4.7 TB/s; runs of 16 to 512 batches an XCD instead of 4 change nothing.  Q6 on 8
 // FP32 vectors (3.4 ms against 6.15 ms): VALU 58 % busy, two wavefronts
 // per SIMD.
 //
