@@ -271,7 +271,7 @@ void set_phases(const LevelDofs& H, std::vector<CellMeta>& meta) {
   std::vector<int32_t> seen(H.n_entities, -1);  // last batch with the entity
   std::vector<uint64_t> used(H.n_entities, 0);  // its phases there
   for (int64_t b = 0; b < H.n_batches; ++b) {
-    int phases = 0;
+    int phases = 0, own = 64;  // (no phase free: one of the cell's own)
     for (int64_t c = H.batch_cell_off[b]; c < H.batch_cell_off[b + 1]; ++c) {
       int32_t ids[26];
       int n = 0;
@@ -284,9 +284,9 @@ void set_phases(const LevelDofs& H, std::vector<CellMeta>& meta) {
         seen[id] = static_cast<int32_t>(b);
         taken |= used[id];
       }
-      MFMG_REQUIRE(taken != ~uint64_t(0), MFMG_ERR_UNSUPPORTED, "deterministic mode: more than 64 phases");
-      const int phase = __builtin_ctzll(~taken);
-      for (int i = 0; i < n; ++i) used[ids[i]] |= uint64_t(1) << phase;
+      const int phase = taken != ~uint64_t(0) ? __builtin_ctzll(~taken) : own++;
+      if (phase < 64)
+        for (int i = 0; i < n; ++i) used[ids[i]] |= uint64_t(1) << phase;
       meta[c].loc[META_PHASE] = static_cast<uint16_t>(phase);
       phases = std::max(phases, phase + 1);
     }
